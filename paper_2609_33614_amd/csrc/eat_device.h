@@ -12,6 +12,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
@@ -120,6 +121,15 @@ __device__ __forceinline__ int tile_group(const int* tstart, int groups, int til
         else lo = mid + 1;
     }
     return lo;
+}
+
+// Lanes of one wave exchanging values through LDS: every lane's stores are
+// ordered before the loads that follow (a wave's LDS operations run in
+// issue order; the fences keep the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Broadcast lane j's value (j uniform across the wave) through an SGPR.

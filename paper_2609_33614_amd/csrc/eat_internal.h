@@ -168,6 +168,36 @@ int up_splits(const eat_params_t& p, int32_t T);
 // bf16 rows and nrm2 [rows][M / 32] partial sums of squares of each row (32
 // features each), taken before the cast.
 bool wide_fits(bool gated, int M, int K);
+// The same kernel's tiles for medium calls: 256 x 128 (`tall`) or 128 x 128;
+// M a multiple of 64, K of 64 and at least 192.  Plain launches (fp32 rows)
+// may slice the reduction dimension, up to max_splits, and write the count
+// taken to splits_out (if set).
+bool mid_fits(int M, int K);
+// Reduction slices of a plain mid-tile launch of `items` work items (one
+// slice each) over `rows` output rows of M: the power of two up to max_splits
+// that makes the launch shortest, in nanoseconds: its rounds over the chip's
+// 256 CUs times a slice's 64-wide chunks (about 600 ns a chunk with 128-row
+// tiles, 900 with 256-row ones) plus every slice's fp32 rows written and read
+// again (about 5 TB/s).  A slice keeps four chunks.  One item too many costs a
+// whole round: the Mixtral-shaped down projection of 500 tokens took 220 us
+// with 8 token tiles (256 items) and 430 with 9 (288).
+__host__ __device__ inline int tile_split(int64_t items, int K, int max_splits, int64_t rows, int M, int chunk_ns) {
+    int best = 1;
+    int64_t least = 0;
+    for (int s = 1; s <= max_splits && (K / 64) % s == 0 && K / 64 / s >= 4; s *= 2) {
+        const int64_t cost = (items * s + 255) / 256 * (K / 64 / s) * chunk_ns + s * rows * M / 625;
+        if (s == 1 || cost < least) {
+            best = s;
+            least = cost;
+        }
+    }
+    return best;
+}
+constexpr int kMidChunkNs = 600, kTallChunkNs = 900;
+hipError_t launch_mid(bool gated, bool tall, const uint16_t* wa, const uint16_t* wb, const uint16_t* src,
+                      const int32_t* gather, const int32_t* offsets, int groups, int nrows, int M, int K,
+                      void* out, int64_t rows_cap, bool packed, int max_splits, int64_t split_stride,
+                      int32_t* splits_out, hipStream_t s);
 hipError_t launch_wide(bool gated, const uint16_t* wa, const uint16_t* wb, const uint16_t* src,
                        const int32_t* gather, const int32_t* offsets, int groups, int nrows, int M,
                        int K, void* out, int64_t rows_cap, bool packed, float* nrm2, hipStream_t s);

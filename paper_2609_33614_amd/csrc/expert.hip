@@ -827,9 +827,37 @@ static bool use_wide(const eat_params_t& p, int32_t T) {
     return p.expert_dtype == EAT_BF16 && static_cast<int64_t>(T) * p.top_k >= int64_t{EAT_WIDE_ROWS} * p.E &&
            wide_fits(true, p.d_ffn, p.d_model) && wide_fits(false, p.d_model, p.d_ffn);
 }
+// Other calls of more than 64 tokens take the medium tiles (wide.hip): their
+// ring keeps 64-96 KB of operands in flight per CU, against 24 KB of weights
+// for the streaming kernel's 128-token tiles.  Measured against those (whole
+// layer): Mixtral-shaped, 500 tokens over 8 experts, 870-890 -> 750-775 us;
+// 128 experts, 1000 tokens, 375 -> 311; 60 experts, 128 tokens, 315 -> 250;
+// 8 of 64 experts, 256 tokens, 89 -> 74.  Up to 64 tokens the streaming
+// kernel reads packed weights at 5.8-6.1 TB/s, the card's rate.
+constexpr int32_t kMidMinTokens = 65;
+static bool use_mid(const eat_params_t& p, int32_t T) {
+    return p.expert_dtype == EAT_BF16 && T >= kMidMinTokens && !use_wide(p, T) && mid_fits(p.d_ffn, p.d_model) &&
+           mid_fits(p.d_model, p.d_ffn);
+}
+// 256-row token tiles where an expert is expected to hold about 100 rows or
+// more (many then exceed 128, and a second 128-row tile reads the weights
+// again: 8 experts of ~125 rows 240 against 335 us down, 495 against 553
+// up/gate) and the up/gate projection's 64-feature items still reach every CU
+// (8 experts of 256 rows, 128 items: 38 against 31 us).
+static bool mid_tall(int64_t groups, int64_t rows, int M) {
+    const int64_t per = (rows + groups - 1) / std::max<int64_t>(1, groups);
+    return per >= 96 && groups * ((per + 255) / 256) * (M / 64) >= 256;
+}
 static bool shared_wide(const eat_params_t& p, int32_t T) {
     return T >= 384 && p.d_shared > 0 && wide_fits(true, p.d_shared, p.d_model) &&
            wide_fits(false, p.d_model, p.d_shared);
+}
+
+// The always-on expert takes them too below its wide-tile size (128 tokens,
+// 5632 wide: no gate/up partials and no reduce launch).
+static bool shared_mid(const eat_params_t& p, int32_t T) {
+    return p.expert_dtype == EAT_BF16 && p.d_shared > 0 && T >= kMidMinTokens && !shared_wide(p, T) &&
+           mid_fits(p.d_shared, p.d_model) && mid_fits(p.d_model, p.d_shared);
 }
 
 bool rows_bf16(const eat_params_t& p, int32_t T) { return use_wide(p, T); }
@@ -863,7 +891,7 @@ static int up_kin(const eat_params_t& p, int32_t T) {
 }
 
 int up_splits(const eat_params_t& p, int32_t T) {
-    if (p.expert_dtype != EAT_BF16 || use_wide(p, T)) return 1;
+    if (p.expert_dtype != EAT_BF16 || use_wide(p, T) || use_mid(p, T)) return 1;
     const int kin = up_kin(p, T);
     return split_rule(p.d_ffn * kin, p.d_model / kin, expected_tiles(p, T), EAT_UP_SPLIT_MAX, up_threshold(T), true);
 }
@@ -935,6 +963,17 @@ hipError_t launch_experts_bf16(const eat_params_t& p, int32_t T, int64_t rows_ca
         return launch_wide(false, w2, nullptr, h, nullptr, offsets, p.E, 0, p.d_model, p.d_ffn, yp, rows_cap, packed,
                            rows_bf16(p, T) ? nrm2 : nullptr, s);
     }
+    if (use_mid(p, T)) {
+        const int64_t assign = static_cast<int64_t>(T) * p.top_k;
+        const bool tall = mid_tall(std::min<int64_t>(p.mode == EAT_MODE_EAT && p.cs_mode == 0 ? p.top_k : p.E, assign),
+                                   assign, p.d_ffn);
+        hipError_t err = launch_mid(true, tall, w1, w3, x, tok_idx, offsets, p.E, 0, p.d_ffn, p.d_model, h, rows_cap, packed,
+                                    1, 0, nullptr, s);
+        if (err != hipSuccess) return err;
+        if (between) between();
+        return launch_mid(false, tall, w2, nullptr, h, nullptr, offsets, p.E, 0, p.d_model, p.d_ffn, yp, rows_cap, packed,
+                          down_splits(p, T), rows_cap * p.d_model, down_splits_dev, s);
+    }
     // both projections take their slices on the device, from the tiles in use
     const int usplits = up_splits(p, T);
     StreamArgs up{};
@@ -982,7 +1021,7 @@ static int shared_up_kin(const eat_params_t& p, int32_t T) {
 }
 
 int shared_up_splits(const eat_params_t& p, int32_t T) {
-    if (p.expert_dtype != EAT_BF16 || p.d_shared == 0 || shared_wide(p, T)) return 1;
+    if (p.expert_dtype != EAT_BF16 || p.d_shared == 0 || shared_wide(p, T) || shared_mid(p, T)) return 1;
     eat_params_t one = p;
     one.E = 1;
     one.top_k = 1;
@@ -993,6 +1032,12 @@ int shared_up_splits(const eat_params_t& p, int32_t T) {
 
 int shared_splits(const eat_params_t& p, int32_t T) {
     if (p.expert_dtype != EAT_BF16 || p.d_shared == 0 || shared_wide(p, T)) return 1;
+    if (shared_mid(p, T)) {
+        const bool tall = mid_tall(1, T, p.d_shared);
+        const int tm = tall ? 256 : 128;
+        return tile_split(static_cast<int64_t>((T + tm - 1) / tm) * ((p.d_model + 127) / 128), p.d_shared,
+                          dense_splits(p.d_model, p.d_shared, T), T, p.d_model, tall ? kTallChunkNs : kMidChunkNs);
+    }
     return dense_splits(p.d_model, p.d_shared, T);
 }
 
@@ -1006,6 +1051,25 @@ hipError_t launch_shared_bf16(const eat_params_t& p, int32_t T, const uint16_t* 
         if (err != hipSuccess) return err;
         return launch_wide(false, ws2, nullptr, hs, nullptr, nullptr, 1, T, p.d_model, p.d_shared, ys, T, packed,
                            nullptr, s);
+    }
+    const int splits = shared_splits(p, T);
+    const int64_t stride = static_cast<int64_t>(T) * p.d_model;
+    float* const dout = splits > 1 ? ysp : ys;
+    auto sum = [&]() {
+        if (splits == 1) return hipSuccess;
+        const int64_t n4 = stride / 4;
+        const int grid = static_cast<int>(std::min<int64_t>((n4 + 255) / 256, 2048));
+        sum_slices_kernel<<<grid, 256, 0, s>>>(ysp, splits, stride, n4, ys);
+        return hipGetLastError();
+    };
+    if (shared_mid(p, T)) {
+        const bool tall = mid_tall(1, T, p.d_shared);
+        hipError_t err = launch_mid(true, tall, ws1, ws3, x, nullptr, nullptr, 1, T, p.d_shared, p.d_model, hs, T,
+                                    packed, 1, 0, nullptr, s);
+        if (err != hipSuccess) return err;
+        err = launch_mid(false, tall, ws2, nullptr, hs, nullptr, nullptr, 1, T, p.d_model, p.d_shared, dout, T, packed,
+                         splits, stride, nullptr, s);
+        return err == hipSuccess ? sum() : err;
     }
     const int nsub = pick_nsub(T);
     const int bn = 16 * nsub;
@@ -1029,18 +1093,13 @@ hipError_t launch_shared_bf16(const eat_params_t& p, int32_t T, const uint16_t* 
         err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
-    const int splits = shared_splits(p, T);
     StreamArgs dn{};
     dn.wa = ws2; dn.wb = nullptr; dn.src = hs; dn.gather = nullptr; dn.offsets = nullptr; dn.nrows = T;
     dn.groups = 1; dn.M = p.d_model; dn.K = p.d_shared; dn.splits = splits;
-    dn.split_stride = static_cast<int64_t>(T) * p.d_model;
-    dn.out = splits > 1 ? ysp : ys;
+    dn.split_stride = stride;
+    dn.out = dout;
     err = launch_stream<false>(dn, nsub, tiles, packed, s);
-    if (err != hipSuccess || splits == 1) return err;
-    const int64_t n4 = dn.split_stride / 4;
-    const int grid = static_cast<int>(std::min<int64_t>((n4 + 255) / 256, 2048));
-    sum_slices_kernel<<<grid, 256, 0, s>>>(ysp, splits, dn.split_stride, n4, ys);
-    return hipGetLastError();
+    return err == hipSuccess ? sum() : err;
 }
 
 }  // namespace eat

@@ -89,16 +89,6 @@ __device__ __forceinline__ float value_at_rank(const float (&v)[J], const int (&
 }
 
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// Lanes of one wave exchanging values through LDS: every lane's stores are
-// ordered before the loads that follow (a wave's LDS operations run in
-// issue order; the fences keep the compiler from moving them).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Order-preserving bits of a non-NaN float: a < b exactly when
 // ord_bits(a) < ord_bits(b); -0 and +0 (equal values) map alike.

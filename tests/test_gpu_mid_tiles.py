@@ -1,0 +1,52 @@
+"""The 128- and 256-row MFMA tiles of medium calls (more than 64 tokens, too
+few rows per expert for the prefill tiles) against the oracle: one token over
+a tile's rows and one under, a last weight tile that ends inside the matrix
+(widths that are odd multiples of 64), the shortest reduction the ring takes
+(192), sliced down projections, an always-on expert, and bit equality between
+the packed and the row-major weights."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_33614_amd import _lib as L
+from paper_2609_33614_amd.layer import EatLayer, pack_weights, to_device
+from tests import test_gpu_parity as P
+from workload import make_accounts
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # 128-row tiles: d = 192 (3 chunks, 64 rows past the second weight tile), F = 320
+    "short": dict(shape="mixtral", d=192, F=320, E=8, Fs=0),
+    # 32 feature tiles x 8 experts: 256-row tiles from ~100 rows per expert
+    "tall": dict(shape="mixtral", d=256, F=2048, E=8, Fs=0),
+    # few rows over many experts, an always-on expert of its own tiles
+    "many": dict(shape="shared", d=320, F=192, E=60, Fs=448),
+}
+
+
+@pytest.mark.parametrize("case,T,mode", [
+    ("short", 65, "topk"), ("short", 128, "eat"), ("short", 129, "eat"), ("short", 513, "topk"),
+    ("tall", 384, "topk"), ("tall", 520, "topp"), ("tall", 900, "eat"), ("tall", 70, "eat"),
+    ("many", 65, "topp"), ("many", 257, "eat"), ("many", 300, "topk"),
+])
+def test_mid_tiles(case, T, mode):
+    c = CASES[case]
+    shape, w, lay, prm = P._layer(c, mode, max_tokens=T)
+    x = P._x_host(shape, T, c["d"], seed=T)
+    acc = make_accounts(c["E"], seed=T, c_scale=0.05)
+    P._forward_check(f"mid {case} {mode} T={T}", lay, shape, x, w, prm, acc=acc)
+
+    wd = to_device(w)
+    p = lay.params
+    outs = []
+    for layout in (L.EAT_LAYOUT_ROWS, L.EAT_LAYOUT_PACKED):
+        q = type(p).from_buffer_copy(p)
+        q.weight_layout = layout
+        lq = EatLayer(q, T, wd if layout == L.EAT_LAYOUT_ROWS else pack_weights(wd))
+        lq.load_accounts(*acc)
+        y = lq.forward(P._x_dev(x))
+        torch.cuda.synchronize()
+        outs.append((y.view(torch.int16).cpu().numpy(), *lq.accounts_host()))
+    for a, b in zip(*outs):
+        np.testing.assert_array_equal(a, b)
