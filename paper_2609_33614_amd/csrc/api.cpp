@@ -305,11 +305,11 @@ hipError_t forward_impl(const eat_ctx& h, const void* x, int32_t T, const float*
     mark(EAT_STAGE_COMBINED);
     if (defer) *defer = AccountJob{};
     if (e == hipSuccess && p.mode == EAT_MODE_EAT) {
-        if (defer)
-            *defer = AccountJob{b.offsets, b.tok_idx, b.prob, b.nrm2, eat::norm_parts(p, T), p.E, p.alpha, acc};
-        else
-            e = eat::launch_update_accounts(p, b.offsets, b.tok_idx, b.prob, b.nrm2, eat::norm_parts(p, T), acc,
-                                            stream);
+        // (the prefill combine leaves a row's sum of squares in its first partial)
+        const int parts = eat::norm_parts(p, T);
+        const AccountJob job{b.offsets, b.tok_idx, b.prob, b.nrm2, rows16 ? 1 : parts, parts, p.E, p.alpha, acc};
+        if (defer) *defer = job;
+        else e = eat::launch_update_accounts(job, T, stream);
     }
     mark(EAT_STAGE_END);
     return e;

@@ -19,7 +19,7 @@
 //   N += n_e,  P_total += sum of the rows' router probabilities,
 //   C_s = (1 - alpha) C_s + alpha * mean row norm,
 // each row norm being sqrt of its partial sums of squares (the combine's
-// slices, or the prefill down projection's 32-feature parts) added in order.
+// slices added in order, or the total the prefill combine leaves).
 // (Doing it in the combine's last workgroup to finish instead of a kernel of
 // its own needs a device-wide release in every combine workgroup, an L2
 // write-back on this part: measured slower at every decode size.)
@@ -43,7 +43,7 @@ struct CombineArgs {
     const float* ys;           // [T][d] shared output or null
     const uint16_t* res;       // [T][d] bf16 residual rows added to y, or null
     void* y;
-    float* nrm2;               // [rows_cap][nchunk] partial sums of squares
+    float* nrm2;               // [rows_cap][nchunk] partial sums of squares, or null: not wanted
     int64_t split_stride;
     int splits, T, E, d, nchunk, words;
 };
@@ -184,6 +184,12 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(CombineArgs a) {
 // per (token, 2048-element slice of d), 8 elements a thread (16-byte loads),
 // every row of a batch of the token's experts loaded before the first is
 // added; the same order of additions as combine_kernel.  y is bf16.
+// For the account update (a.nrm2 set) the token's first workgroup also adds up
+// each of its rows' nchunk partial sums of squares, one wave a row and a
+// lane per partial, and leaves the total in the row's first one: the update
+// then reads one value a row.  (It used to read all 64 itself, one workgroup
+// per expert: 144 us of a 8192-token call whose tokens share 4 experts, now
+// under 10.)
 constexpr int kRowVec = 8;
 __global__ __launch_bounds__(kThreads) void combine_rows16_kernel(CombineArgs a) {
     const int t = blockIdx.x;
@@ -230,6 +236,18 @@ __global__ __launch_bounds__(kThreads) void combine_rows16_kernel(CombineArgs a)
             }
         }
         if (nb == 0) break;
+        if (a.nrm2 && blockIdx.y == 0) {      // uniform
+            const int lane = lane_id(), wave = threadIdx.x / kWave;
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                if (b >= nb || b % kWaves != wave) continue;
+                float* const rp = a.nrm2 + static_cast<int64_t>(rows[b]) * a.nchunk;
+                float ss = 0.f;
+                for (int c = lane; c < a.nchunk; c += kWave) ss += rp[c];
+                ss = wave_sum(ss);            // every lane's loads are done: the total may take the first's place
+                if (lane == 0) rp[0] = ss;
+            }
+        }
         // (rows past nb read row 0, unused)
         uint4 q[kBatch];
 #pragma unroll
@@ -265,14 +283,19 @@ __global__ __launch_bounds__(kThreads) void combine_rows16_kernel(CombineArgs a)
     *reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.y) + static_cast<size_t>(t) * a.d + kRowVec * j) = pk;
 }
 
-// Expert e's account update by one workgroup (every thread of it calls this).
+// Expert e's account update by one workgroup of NT threads (every thread of
+// it calls this).  A thread takes every NT-th row of the expert's segment; in
+// prefill-sized updates (NT = 1024) four of them per round of loads, as a row
+// is a chain of two: its token, then the token's probability.
+template <int NT>
 __device__ __forceinline__ void account_update(const AccountJob& j, int e) {
-    __shared__ double red[2][kWaves];
+    constexpr int kW = NT / kWave, kRows = NT > kThreads ? 4 : 1;
+    __shared__ double red[2][kW];
     const int32_t* __restrict__ offsets = j.offsets;
     const int32_t* __restrict__ tok_idx = j.tok_idx;
     const float* __restrict__ prob = j.prob;
     const float* __restrict__ nrm2 = j.nrm2;
-    const int nchunk = j.parts, E = j.experts;
+    const int parts = j.parts, stride = j.stride, E = j.experts;
     const float alpha = j.alpha;
     int64_t* __restrict__ n = j.acc.n;
     float* __restrict__ p_total = j.acc.p_total;
@@ -282,20 +305,24 @@ __device__ __forceinline__ void account_update(const AccountJob& j, int e) {
     const int cnt = end - beg;
     if (cnt <= 0) return;
     double sp = 0.0, sn = 0.0;
-    for (int r = beg + threadIdx.x; r < end; r += kThreads) {
-        sp += static_cast<double>(prob[static_cast<size_t>(tok_idx[r]) * E + e]);
-        float ss = 0.f;
-        const float* rp = nrm2 + static_cast<size_t>(r) * nchunk;
-        if ((nchunk & 3) == 0) {
-            // (the same order, four partials per load)
-            for (int c = 0; c < nchunk; c += 4) {
-                const float4 v = *reinterpret_cast<const float4*>(rp + c);
-                ss += v.x; ss += v.y; ss += v.z; ss += v.w;
-            }
-        } else {
-            for (int c = 0; c < nchunk; ++c) ss += rp[c];
+    for (int r0 = beg + threadIdx.x; r0 < end; r0 += kRows * NT) {
+        int tok[kRows];
+        float pr[kRows], ss[kRows];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) tok[u] = tok_idx[min(r0 + u * NT, end - 1)];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            pr[u] = prob[static_cast<size_t>(tok[u]) * E + e];
+            const float* rp = nrm2 + static_cast<size_t>(min(r0 + u * NT, end - 1)) * stride;
+            ss[u] = rp[0];
+            for (int c = 1; c < parts; ++c) ss[u] += rp[c];
         }
-        sn += static_cast<double>(sqrtf(ss));
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            if (r0 + u * NT >= end) break;
+            sp += static_cast<double>(pr[u]);
+            sn += static_cast<double>(sqrtf(ss[u]));
+        }
     }
     sp = wave_sum(sp);
     sn = wave_sum(sn);
@@ -304,7 +331,7 @@ __device__ __forceinline__ void account_update(const AccountJob& j, int e) {
     if (threadIdx.x == 0) {
         double tp = 0.0, tn = 0.0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) { tp += red[0][w]; tn += red[1][w]; }
+        for (int w = 0; w < kW; ++w) { tp += red[0][w]; tn += red[1][w]; }
         n[e] += cnt;
         p_total[e] = static_cast<float>(static_cast<double>(p_total[e]) + tp);
         const double a = static_cast<double>(alpha);
@@ -312,7 +339,8 @@ __device__ __forceinline__ void account_update(const AccountJob& j, int e) {
     }
 }
 
-__global__ __launch_bounds__(kThreads) void update_accounts_kernel(AccountJob j) { account_update(j, blockIdx.x); }
+template <int NT>
+__global__ __launch_bounds__(NT) void update_accounts_kernel(AccountJob j) { account_update<NT>(j, blockIdx.x); }
 
 // One workgroup per token row of d <= kMixMax elements: v = the row's
 // split partials added in split order (or the bf16 source row), h = bf16(v)
@@ -332,7 +360,7 @@ __global__ __launch_bounds__(kThreads) void mix_norm_kernel(const float* __restr
     __shared__ float red[kWaves];
     const int t = blockIdx.x;
     if (t >= T) {                             // uniform over the workgroup
-        account_update(job, t - T);
+        account_update<kThreads>(job, t - T);
         return;
     }
     const int lane = lane_id(), wave = threadIdx.x / kWave;
@@ -415,6 +443,8 @@ hipError_t launch_combine(const eat_params_t& p, int32_t T, const uint64_t* mask
     a.y = y; a.nrm2 = nrm2; a.split_stride = split_stride; a.splits = splits; a.T = T; a.E = p.E; a.d = p.d_model;
     a.nchunk = nchunk; a.words = mask_words(p.E);
     if (rows_bf16) {
+        a.nchunk = p.d_model / 32;
+        if (p.mode != EAT_MODE_EAT) a.nrm2 = nullptr;
         const int n8 = (p.d_model / kRowVec + kThreads - 1) / kThreads;
         combine_rows16_kernel<<<dim3(T, n8), kThreads, 0, s>>>(a);
         return hipGetLastError();
@@ -425,9 +455,10 @@ hipError_t launch_combine(const eat_params_t& p, int32_t T, const uint64_t* mask
     return hipGetLastError();
 }
 
-hipError_t launch_update_accounts(const eat_params_t& p, const int32_t* offsets, const int32_t* tok_idx,
-                                  const float* prob, const float* nrm2, int parts, eat_accounts_t acc, hipStream_t s) {
-    update_accounts_kernel<<<p.E, kThreads, 0, s>>>(AccountJob{offsets, tok_idx, prob, nrm2, parts, p.E, p.alpha, acc});
+hipError_t launch_update_accounts(const AccountJob& job, int32_t T, hipStream_t s) {
+    // (an expert holds at most T rows)
+    if (T > 4 * kThreads) update_accounts_kernel<1024><<<job.experts, 1024, 0, s>>>(job);
+    else update_accounts_kernel<kThreads><<<job.experts, kThreads, 0, s>>>(job);
     return hipGetLastError();
 }
 

@@ -233,7 +233,7 @@ struct AccountJob {
     const int32_t* tok_idx;
     const float* prob;
     const float* nrm2;
-    int parts;               // partial sums of squares per row in nrm2
+    int parts, stride;       // partial sums of squares to add per row, and floats between rows in nrm2
     int experts;
     float alpha;
     eat_accounts_t acc;
@@ -247,9 +247,6 @@ hipError_t forward_impl(const eat_ctx& h, const void* x, int32_t T, const float*
                         hipStream_t stream, const hipEvent_t* events, int32_t n_events,
                         AccountJob* defer = nullptr);
 
-// nrm2: `parts` partial sums of squares per row, added in order.
-hipError_t launch_update_accounts(const eat_params_t& p, const int32_t* offsets,
-                                  const int32_t* tok_idx, const float* prob, const float* nrm2, int parts,
-                                  eat_accounts_t acc, hipStream_t s);
+hipError_t launch_update_accounts(const AccountJob& job, int32_t T, hipStream_t s);
 
 }  // namespace eat
