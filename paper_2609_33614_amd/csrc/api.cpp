@@ -77,7 +77,6 @@ Workspace plan_workspace(const eat_ctx& c, int32_t T) {
     w.offsets = take((E + 1) * 4);
     w.tok_idx = take(rows * 4);
     w.inv = take(t * E * 4);
-    w.row_expert = take(rows * 4);
     w.h = take(rows * p.d_ffn * es);
     w.gu = take(w.up_splits > 1 ? 2 * static_cast<size_t>(w.up_splits) * rows * p.d_ffn * 4 : 0);
     w.yp = take(static_cast<size_t>(w.splits) * rows * p.d_model * 4);
@@ -244,7 +243,6 @@ hipError_t forward_impl(const eat_ctx& h, const void* x, int32_t T, const float*
     b.offsets = reinterpret_cast<int32_t*>(base + w.offsets);
     b.tok_idx = reinterpret_cast<int32_t*>(base + w.tok_idx);
     b.inv = reinterpret_cast<int32_t*>(base + w.inv);
-    b.row_expert = reinterpret_cast<int32_t*>(base + w.row_expert);
     b.h = base + w.h;
     b.gu = reinterpret_cast<float*>(base + w.gu);
     b.yp = reinterpret_cast<float*>(base + w.yp);
@@ -266,8 +264,7 @@ hipError_t forward_impl(const eat_ctx& h, const void* x, int32_t T, const float*
         e = eat::launch_route(p, x, T, w_router, acc, ppl_trend, b.lpart, b.mask, b.k, b.gate, b.prob, stream);
     mark(EAT_STAGE_ROUTED);
     if (e == hipSuccess)
-        e = eat::launch_permute(p, T, b.mask, b.offsets, b.tok_idx, b.inv, b.row_expert, expert_load_out,
-                                stream);
+        e = eat::launch_permute(p, T, b.mask, b.offsets, b.tok_idx, b.inv, expert_load_out, stream);
     mark(EAT_STAGE_PERMUTED);
     const bool bf16 = p.expert_dtype == EAT_BF16;
     if (e == hipSuccess) {
@@ -280,7 +277,7 @@ hipError_t forward_impl(const eat_ctx& h, const void* x, int32_t T, const float*
         else
             e = eat::launch_experts_f32(p, T, w.rows, static_cast<const float*>(x),
                                         static_cast<const float*>(w1), static_cast<const float*>(w3),
-                                        static_cast<const float*>(w2), b.offsets, b.tok_idx, b.row_expert,
+                                        static_cast<const float*>(w2), b.offsets, b.tok_idx,
                                         static_cast<float*>(b.h), b.yp, stream, [&]() { mark(EAT_STAGE_UP); });
     }
     mark(EAT_STAGE_DOWN);

@@ -31,7 +31,7 @@ inline int mask_words(int E) { return (E + 63) / 64; }
 constexpr int kSyncWords = 2;
 
 struct Workspace {
-    size_t lpart, prob, gate, mask, k, offsets, tok_idx, inv, row_expert, h, gu, yp, nrm, hs, ys, gus, ysp, sync;
+    size_t lpart, prob, gate, mask, k, offsets, tok_idx, inv, h, gu, yp, nrm, hs, ys, gus, ysp, sync;
     size_t route_total;      // bytes eat_route needs (the leading lpart region)
     size_t total;
     int64_t rows;            // capacity in (token, expert) rows = T * kmax
@@ -52,7 +52,6 @@ struct Buffers {
     int32_t* offsets;        // [E+1] expert-major row offsets
     int32_t* tok_idx;        // [rows] token of each expert-major row
     int32_t* inv;            // [T][E] row of (t, e), valid where selected
-    int32_t* row_expert;     // [rows] expert of each row
     void* h;                 // [rows][F] SwiGLU hidden (bf16 or fp32)
     float* gu;               // [2][up_splits][rows][F] gate / up partial sums
     float* yp;               // [splits][rows][d] un-gated expert outputs (partials)
@@ -77,16 +76,14 @@ int route_token_tiles(int32_t T);                  // 16-token MFMA tiles per lo
 int route_slices(const eat_params_t& p, int32_t T);  // d slices of the logits kernel
 
 hipError_t launch_permute(const eat_params_t& p, int32_t T, const uint64_t* mask,
-                          int32_t* offsets, int32_t* tok_idx, int32_t* inv, int32_t* row_expert,
-                          int32_t* expert_load, hipStream_t s);
+                          int32_t* offsets, int32_t* tok_idx, int32_t* inv, int32_t* expert_load, hipStream_t s);
 
 // Routed experts.  `between` runs on the host after the up/gate launch and
 // before the down launch (stage-event hook).
 // fp32 weights and activations (small layers):
 hipError_t launch_experts_f32(const eat_params_t& p, int32_t T, int64_t rows_cap, const float* x,
                               const float* w1, const float* w3, const float* w2,
-                              const int32_t* offsets, const int32_t* tok_idx,
-                              const int32_t* row_expert, float* h, float* yp, hipStream_t s,
+                              const int32_t* offsets, const int32_t* tok_idx, float* h, float* yp, hipStream_t s,
                               const std::function<void()>& between);
 
 // bf16 weights and activations: MFMA kernels.  Both projections choose

@@ -22,8 +22,8 @@
 // Prefill-sized calls (hundreds of rows per expert) go to the wide MFMA
 // tiles of wide.hip instead.
 //
-// fp32 path: plain dot products, one thread per output element, for layers
-// whose weights are fp32 (small correctness-sized layers).
+// fp32 path: fp32 MFMA tiles, for layers whose weights are fp32 (small
+// correctness-sized layers).
 #include <algorithm>
 #include <type_traits>
 
@@ -35,68 +35,146 @@ namespace {
 
 // ---------------------------------------------------------------- fp32 --
 
+// One workgroup of 4 waves per (tile of up to 64 tokens, 16 weight rows): the
+// waves take interleaved 16-wide k-steps of the whole reduction with
+// v_mfma_f32_16x16x4_f32 (weights as A, tokens as B, fp32 throughout) and add
+// their tiles in wave order through LDS, wave w finishing token group w.
+// These layers are small (the tiny one: 8 experts of ~8 rows, 256 x 128), so
+// a launch is a chain of latencies: every load of up to four k-steps is issued
+// before the first MFMA and no wave's chain is longer than a quarter of the
+// reduction.  Against one thread per output element, each walking its own
+// weight row: 33 -> 4 us up/gate, 35 -> 4 us down on the tiny layer.
 struct F32Args {
-    const float* x;            // [*, d] token activations
-    const float* w1;           // [E][F][d]
-    const float* w3;
-    const float* w2;           // [E][d][F]
-    const int32_t* tok_idx;    // row -> token, or null (row == token)
-    const int32_t* row_expert; // row -> expert, or null (expert 0)
-    const int32_t* rows_dev;   // device row count (offsets[E]), or null
-    int rows_host;             // row count when rows_dev is null
-    int d, F;
-    float* h;                  // [rows][F]
-    float* yp;                 // [rows][d]
+    const float* wa;           // [E][M][K]
+    const float* wb;           // [E][M][K], gated only
+    const float* src;          // activation rows, K wide
+    const int32_t* gather;     // row -> source row, or null (identity)
+    const int32_t* offsets;    // [groups+1] expert-major row offsets, or null
+    int nrows;                 // rows of the single group when offsets is null
+    int groups, M, K;
+    float* out;                // [rows][M]
 };
 
-__global__ __launch_bounds__(256) void ffn_up_f32(F32Args a) {
-    const int64_t rows = a.rows_dev ? *a.rows_dev : a.rows_host;
-    const int64_t total = rows * a.F;
-    for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < total;
-         i += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t r = i / a.F;
-        const int f = static_cast<int>(i % a.F);
-        const int t = a.tok_idx ? a.tok_idx[r] : static_cast<int>(r);
-        const int e = a.row_expert ? a.row_expert[r] : 0;
-        const float* xr = a.x + static_cast<size_t>(t) * a.d;
-        const float* g = a.w1 + (static_cast<size_t>(e) * a.F + f) * a.d;
-        const float* u = a.w3 + (static_cast<size_t>(e) * a.F + f) * a.d;
-        float sg = 0.f, su = 0.f;
-        for (int k = 0; k < a.d; ++k) {
-            sg = fmaf(xr[k], g[k], sg);
-            su = fmaf(xr[k], u[k], su);
+constexpr int kF32Waves = 4, kF32Tok = 64;
+
+template <bool GATED>
+__global__ __launch_bounds__(kF32Waves * kWave) void ffn_f32_kernel(F32Args a) {
+    constexpr int NM = GATED ? 2 : 1, TT = kF32Tok / 16;
+    __shared__ f32x4 red[kF32Waves][NM][TT][kWave];
+    __shared__ int tstart[kMaxExperts + 1];
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    const int i16 = lane & 15, kq = 4 * (lane >> 4);
+    int ntiles;
+    if (a.offsets) {
+        tile_starts(a.offsets, a.groups, kF32Tok, tstart);
+        ntiles = tstart[a.groups];
+    } else {
+        ntiles = (a.nrows + kF32Tok - 1) / kF32Tok;
+    }
+    const int nrb = a.M / 16;
+    const int64_t items = static_cast<int64_t>(ntiles) * nrb;
+    for (int64_t w = blockIdx.x; w < items; w += gridDim.x) {
+        const int tile = static_cast<int>(w / nrb), m0 = static_cast<int>(w % nrb) * 16;
+        int e = 0, r0, n;
+        if (a.offsets) {
+            e = tile_group(tstart, a.groups, tile);
+            r0 = a.offsets[e] + (tile - tstart[e]) * kF32Tok;
+            n = min(kF32Tok, a.offsets[e + 1] - r0);
+        } else {
+            r0 = tile * kF32Tok;
+            n = min(kF32Tok, a.nrows - r0);
         }
-        a.h[r * a.F + f] = silu(sg) * su;
+        const int ntt = (n + 15) / 16;        // token groups in use (uniform)
+        const size_t wrow = (static_cast<size_t>(e) * a.M + m0 + i16) * a.K + kq;
+        const float* const wp[2] = {a.wa + wrow, GATED ? a.wb + wrow : nullptr};
+        const float* xp[TT];
+#pragma unroll
+        for (int t = 0; t < TT; ++t) {
+            // (rows past the tile read its first row; their columns are not stored)
+            const int r = r0 + (16 * t + i16 < n ? 16 * t + i16 : 0);
+            xp[t] = a.src + static_cast<size_t>(a.gather ? a.gather[r] : r) * a.K + kq;
+        }
+        f32x4 acc[NM][TT];
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int t = 0; t < TT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // this wave's k-steps: wave, wave + 4, ... (K is a multiple of 64), U at a time
+        auto steps = [&](int k0, auto u_tag) __attribute__((always_inline)) {
+            constexpr int U = decltype(u_tag)::value;
+            f32x4 W[U][NM], X[U][TT];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + 64 * u;
+#pragma unroll
+                for (int m = 0; m < NM; ++m) W[u][m] = *reinterpret_cast<const f32x4*>(wp[m] + k);
+#pragma unroll
+                for (int t = 0; t < TT; ++t)
+                    if (t < ntt) X[u][t] = *reinterpret_cast<const f32x4*>(xp[t] + k);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int t = 0; t < TT; ++t) {
+                    if (t >= ntt) break;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int m = 0; m < NM; ++m)
+                            acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[u][m][q], X[u][t][q], acc[m][t], 0, 0, 0);
+                }
+        };
+        int k = 16 * wave;
+        for (; k + 64 < a.K; k += 128) steps(k, std::integral_constant<int, 2>{});
+        if (k < a.K) steps(k, std::integral_constant<int, 1>{});
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int t = 0; t < TT; ++t)
+                if (t < ntt) red[wave][m][t][lane] = acc[m][t];
+        __syncthreads();
+        // lane holds weight rows m0 + 4 (lane / 16) + q of token column lane % 16
+        if (wave < ntt) {
+            f32x4 s[NM];
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                s[m] = red[0][m][wave][lane];
+#pragma unroll
+                for (int v = 1; v < kF32Waves; ++v) s[m] += red[v][m][wave][lane];
+            }
+            const int c = 16 * wave + i16;
+            if (c < n) {
+                f32x4 o = s[0];
+                if constexpr (GATED) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) o[q] = silu(s[0][q]) * s[1][q];
+                }
+                *reinterpret_cast<f32x4*>(a.out + static_cast<size_t>(r0 + c) * a.M + m0 + kq) = o;
+            }
+        }
+        __syncthreads();
     }
 }
 
-__global__ __launch_bounds__(256) void ffn_down_f32(F32Args a) {
-    const int64_t rows = a.rows_dev ? *a.rows_dev : a.rows_host;
-    const int64_t total = rows * a.d;
-    for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < total;
-         i += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t r = i / a.d;
-        const int j = static_cast<int>(i % a.d);
-        const int e = a.row_expert ? a.row_expert[r] : 0;
-        const float* hr = a.h + r * a.F;
-        const float* w = a.w2 + (static_cast<size_t>(e) * a.d + j) * a.F;
-        float s = 0.f;
-        for (int f = 0; f < a.F; ++f) s = fmaf(hr[f], w[f], s);
-        a.yp[r * a.d + j] = s;
-    }
+template <bool GATED>
+hipError_t launch_ffn_f32(const F32Args& a, int64_t max_tiles, hipStream_t s) {
+    const int64_t items = max_tiles * (a.M / 16);
+    const int grid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(items, 2048)));
+    ffn_f32_kernel<GATED><<<grid, kF32Waves * kWave, 0, s>>>(a);
+    return hipGetLastError();
 }
 
-hipError_t launch_f32_pair(F32Args a, int64_t rows_cap, hipStream_t s,
+// Up/gate then down of one layer's rows (routed, or all T of the always-on
+// expert when offsets is null).
+hipError_t launch_f32_pair(const float* x, const float* w1, const float* w3, const float* w2,
+                           const int32_t* tok_idx, const int32_t* offsets, int nrows, int groups, int d, int F,
+                           int64_t max_tiles, float* h, float* yp, hipStream_t s,
                            const std::function<void()>& between) {
-    const int64_t up = rows_cap * a.F, dn = rows_cap * a.d;
-    const int gu = static_cast<int>(std::min<int64_t>((up + 255) / 256, 8192));
-    const int gd = static_cast<int>(std::min<int64_t>((dn + 255) / 256, 8192));
-    if (gu > 0) ffn_up_f32<<<gu, 256, 0, s>>>(a);
-    hipError_t err = hipGetLastError();
+    const hipError_t err =
+        launch_ffn_f32<true>(F32Args{w1, w3, x, tok_idx, offsets, nrows, groups, F, d, h}, max_tiles, s);
     if (err != hipSuccess) return err;
     if (between) between();
-    if (gd > 0) ffn_down_f32<<<gd, 256, 0, s>>>(a);
-    return hipGetLastError();
+    return launch_ffn_f32<false>(F32Args{w2, nullptr, h, nullptr, offsets, nrows, groups, d, F, yp}, max_tiles, s);
 }
 
 // ------------------------------------------------------- bf16 streaming --
@@ -928,19 +1006,18 @@ hipError_t launch_dense_bf16(const uint16_t* src, int32_t T, const uint16_t* w, 
 
 hipError_t launch_experts_f32(const eat_params_t& p, int32_t T, int64_t rows_cap, const float* x,
                               const float* w1, const float* w3, const float* w2,
-                              const int32_t* offsets, const int32_t* tok_idx,
-                              const int32_t* row_expert, float* h, float* yp, hipStream_t s,
+                              const int32_t* offsets, const int32_t* tok_idx, float* h, float* yp, hipStream_t s,
                               const std::function<void()>& between) {
-    F32Args a{x, w1, w3, w2, tok_idx, row_expert, offsets + p.E, 0, p.d_model, p.d_ffn, h, yp};
-    (void)T;
-    return launch_f32_pair(a, rows_cap, s, between);
+    const int64_t per_expert = (T + kF32Tok - 1) / kF32Tok;
+    const int64_t tiles = std::min<int64_t>({rows_cap, per_expert * p.E, (rows_cap + kF32Tok - 1) / kF32Tok + p.E});
+    return launch_f32_pair(x, w1, w3, w2, tok_idx, offsets, 0, p.E, p.d_model, p.d_ffn, tiles, h, yp, s, between);
 }
 
 hipError_t launch_shared_f32(const eat_params_t& p, int32_t T, const float* x, const float* ws1,
                              const float* ws3, const float* ws2, float* hs, float* ys,
                              hipStream_t s) {
-    F32Args a{x, ws1, ws3, ws2, nullptr, nullptr, nullptr, T, p.d_model, p.d_shared, hs, ys};
-    return launch_f32_pair(a, T, s, nullptr);
+    return launch_f32_pair(x, ws1, ws3, ws2, nullptr, nullptr, T, 1, p.d_model, p.d_shared,
+                           (T + kF32Tok - 1) / kF32Tok, hs, ys, s, nullptr);
 }
 
 hipError_t launch_experts_bf16(const eat_params_t& p, int32_t T, int64_t rows_cap, const uint16_t* x,

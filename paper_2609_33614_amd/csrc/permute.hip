@@ -23,8 +23,7 @@ constexpr int kWaves = kThreads / kWave;
 template <int PRE>
 __global__ __launch_bounds__(kThreads) void permute_kernel(
     const uint64_t* __restrict__ mask, int T, int E, int W, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ tok_idx, int32_t* __restrict__ inv, int32_t* __restrict__ row_expert,
-    int32_t* __restrict__ expert_load) {
+    int32_t* __restrict__ tok_idx, int32_t* __restrict__ inv, int32_t* __restrict__ expert_load) {
     __shared__ int red[2][kWaves];
     __shared__ int wtot[kWaves];
     const int e = blockIdx.x;
@@ -101,7 +100,6 @@ __global__ __launch_bounds__(kThreads) void permute_kernel(
             if (on) {
                 const int row = off + running + pre + __popcll(b & lt);
                 tok_idx[row] = t;
-                row_expert[row] = e;
                 inv[static_cast<size_t>(t) * E + e] = row;
             }
             running += all;
@@ -113,14 +111,13 @@ __global__ __launch_bounds__(kThreads) void permute_kernel(
 }  // namespace
 
 hipError_t launch_permute(const eat_params_t& p, int32_t T, const uint64_t* mask, int32_t* offsets,
-                          int32_t* tok_idx, int32_t* inv, int32_t* row_expert, int32_t* expert_load,
-                          hipStream_t s) {
+                          int32_t* tok_idx, int32_t* inv, int32_t* expert_load, hipStream_t s) {
     if (T <= kThreads)
         permute_kernel<1><<<dim3(p.E), dim3(kThreads), 0, s>>>(mask, T, p.E, mask_words(p.E), offsets, tok_idx,
-                                                               inv, row_expert, expert_load);
+                                                               inv, expert_load);
     else
         permute_kernel<16><<<dim3(p.E), dim3(kThreads), 0, s>>>(mask, T, p.E, mask_words(p.E), offsets, tok_idx,
-                                                                inv, row_expert, expert_load);
+                                                                inv, expert_load);
     return hipGetLastError();
 }
 
