@@ -475,7 +475,7 @@ eat_status_t eat_pack_weights(const void* src, int32_t groups, int32_t M, int32_
 eat_status_t eat_ppl_workspace_size(int32_t S, int32_t d, int32_t V, size_t* bytes) {
     if (!bytes || S < 0 || S > kMaxTokens || d < 64 || d % 64 || V < 64 || V % 64) return EAT_ERR_INVALID_ARG;
     if (static_cast<int64_t>(d) * V >= (int64_t{1} << 31)) return EAT_ERR_INVALID_ARG;
-    *bytes = align256(static_cast<size_t>(eat::ppl_splits(S, d, V)) * S * V * 4) +
+    *bytes = align256(static_cast<size_t>(eat::head_splits(V, d, S)) * S * V * 4) +
              align256(static_cast<size_t>(S) * eat::ppl_chunks(V) * 8);
     return EAT_OK;
 }
@@ -502,11 +502,11 @@ eat_status_t eat_ppl_trend(const void* h, int32_t S, int32_t d, const void* w_vo
     if (!ws || ws_bytes < need) return EAT_ERR_WORKSPACE;
     if (!aligned(ws, 256)) return EAT_ERR_INVALID_ARG;
     float* z = static_cast<float*>(ws);
-    const int splits = eat::ppl_splits(S, d, V);
+    const int splits = eat::head_splits(V, d, S);
     const int64_t stride = static_cast<int64_t>(S) * V;
     (void)hipGetLastError();
-    hipError_t e = eat::launch_dense_bf16(static_cast<const uint16_t*>(h), S, static_cast<const uint16_t*>(w_vocab),
-                                          V, d, z, splits, stride, stream);
+    hipError_t e = eat::launch_head_bf16(static_cast<const uint16_t*>(h), S, static_cast<const uint16_t*>(w_vocab),
+                                         V, d, z, splits, stride, stream);
     if (e == hipSuccess)
         e = eat::launch_ppl(z, splits, stride, S, V, target, nll_sum, count, ppl_prev, trend_out, nll_out,
                             reinterpret_cast<float2*>(static_cast<char*>(ws) +

@@ -139,6 +139,10 @@ hipError_t launch_mix_norm(const float* part, int splits, int64_t split_stride, 
 int dense_splits(int M, int K, int32_t T);
 hipError_t launch_dense_bf16(const uint16_t* src, int32_t T, const uint16_t* w, int M, int K, float* out,
                              int splits, int64_t split_stride, hipStream_t s);
+// The same for an LM head [M][K] (ppl): its own choice of tiles and slices.
+int head_splits(int M, int K, int32_t T);
+hipError_t launch_head_bf16(const uint16_t* src, int32_t T, const uint16_t* w, int M, int K, float* out,
+                            int splits, int64_t split_stride, hipStream_t s);
 // 1024-element slices of d the combine works in.
 int combine_chunks(const eat_params_t& p);
 // Prefill-sized bf16 calls: the down projection (wide tiles) stores the
@@ -210,7 +214,6 @@ hipError_t launch_pack(const uint16_t* src, int32_t groups, int32_t M, int32_t K
 hipError_t launch_ppl(const float* z, int splits, int64_t stride, int32_t S, int V, const int32_t* target,
                       double* nll_sum, int32_t* count, double* ppl_prev, int8_t* trend, float* nll_out,
                       float2* part, hipStream_t s);
-int ppl_splits(int32_t S, int d, int V);
 int ppl_chunks(int V);                 // (max, sum) pairs per row in `part`
 hipError_t launch_ppl_reset(int32_t S, double* nll_sum, int32_t* count, double* ppl_prev, hipStream_t s);
 

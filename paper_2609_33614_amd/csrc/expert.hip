@@ -1004,6 +1004,27 @@ hipError_t launch_dense_bf16(const uint16_t* src, int32_t T, const uint16_t* w, 
     return launch_stream<false>(a, nsub, tiles, false, s);
 }
 
+// LM-head projection: the medium tiles, one slice, below the wide-tile size.
+// The head is row-major and read once: 64 sequences x 32000 x 4096 took 67 us
+// (3.9 TB/s) in the streaming kernel's two slices and the whole signal 72.6; on
+// the tiles 59.1 (1 sequence 63.6 -> 54.9, 200 sequences, on 256-row tiles,
+// 147 -> 101, 383 205 -> 178).
+static bool head_mid(int M, int K, int32_t T) { return !dense_wide(M, K, T) && mid_fits(M, K); }
+
+// Most slices of the head where the streaming kernel runs it (each costs one
+// more S x V fp32 read in the logsumexp).
+constexpr int kHeadSplitsMax = 2;
+int head_splits(int M, int K, int32_t T) {
+    return head_mid(M, K, T) ? 1 : std::min(dense_splits(M, K, T), kHeadSplitsMax);
+}
+
+hipError_t launch_head_bf16(const uint16_t* src, int32_t T, const uint16_t* w, int M, int K, float* out,
+                            int splits, int64_t split_stride, hipStream_t s) {
+    if (head_mid(M, K, T))
+        return launch_mid(false, T > 128, w, nullptr, src, nullptr, nullptr, 1, T, M, K, out, T, false, 1, 0, nullptr, s);
+    return launch_dense_bf16(src, T, w, M, K, out, splits, split_stride, s);
+}
+
 hipError_t launch_experts_f32(const eat_params_t& p, int32_t T, int64_t rows_cap, const float* x,
                               const float* w1, const float* w3, const float* w2,
                               const int32_t* offsets, const int32_t* tok_idx, float* h, float* yp, hipStream_t s,

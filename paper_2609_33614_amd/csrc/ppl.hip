@@ -1,9 +1,9 @@
 // Perplexity signal for the threshold's performance-based adjustment
 // (Sec. 3.3), gfx950.
 //
-// The LM-head projection z = h W_V^T runs on the dense bf16 stream / wide
-// kernels (expert.hip, wide.hip) into fp32 rows (slices of the reduction
-// dimension at decode sizes, added in order here).  ppl_chunk_kernel folds
+// The LM-head projection z = h W_V^T runs on the MFMA tiles (wide.hip) into
+// fp32 rows, or on the streaming kernel (expert.hip) where the reduction is too
+// short for them (up to two slices of it, added in order here).  ppl_chunk_kernel folds
 // each of up to 16 vocabulary chunks of a row into an online logsumexp
 // pair (running max, sum of exp(z - max)) in one pass; ppl_finish_kernel
 // merges a row's chunks in order and forms NLL = logsumexp - z[target] and
@@ -124,13 +124,6 @@ hipError_t launch_ppl(const float* z, int splits, int64_t stride, int32_t S, int
                                                                          nll_sum, count, ppl_prev, trend, nll_out);
     return hipGetLastError();
 }
-
-// Reduction slices of the LM-head GEMM: the dense heuristic, capped (each
-// slice costs one more S x V fp32 read in the logsumexp).
-#ifndef EAT_PPL_SPLITS_MAX
-#define EAT_PPL_SPLITS_MAX 2
-#endif
-int ppl_splits(int32_t S, int d, int V) { return std::min(dense_splits(V, d, S), EAT_PPL_SPLITS_MAX); }
 
 hipError_t launch_ppl_reset(int32_t S, double* nll_sum, int32_t* count, double* ppl_prev, hipStream_t s) {
     ppl_reset_kernel<<<(S + kThreads - 1) / kThreads, kThreads, 0, s>>>(S, nll_sum, count, ppl_prev);

@@ -9,7 +9,7 @@ import pytest
 import torch
 
 from paper_2609_33614_amd import _lib as L
-from paper_2609_33614_amd.layer import EatLayer, pack_weights, to_device
+from paper_2609_33614_amd.layer import EatLayer, PplSignal, pack_weights, to_device
 from tests import test_gpu_parity as P
 from workload import make_accounts
 
@@ -50,3 +50,24 @@ def test_mid_tiles(case, T, mode):
         outs.append((y.view(torch.int16).cpu().numpy(), *lq.accounts_host()))
     for a, b in zip(*outs):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("S,d,V", [(1, 192, 64), (16, 256, 960), (128, 192, 320), (129, 512, 1088), (383, 256, 448),
+                                   (3, 128, 64)])
+def test_head_tiles(S, d, V):
+    """The LM head of the perplexity signal on the same tiles (d = 128: on the
+    streaming kernel), against float64.  An fp32 sum of d products of bf16
+    values is off by at most d 2^-24 sum |h w|, and a logsumexp by no more than
+    its logits plus a few fp32 roundings of its value."""
+    g = torch.Generator().manual_seed(S + d + V)
+    head = (torch.randn(V, d, generator=g) * d ** -0.5).to(torch.bfloat16)
+    h = torch.randn(S, d, generator=g).to(torch.bfloat16)
+    target = torch.randint(0, V, (S,), generator=g).to(torch.int32)
+    sig = PplSignal(S, head.cuda())
+    sig.reset()
+    sig.step(h.cuda(), target.cuda())
+    torch.cuda.synchronize()
+    z = h.double() @ head.double().T
+    nll = torch.logsumexp(z, 1) - z.gather(1, target.long()[:, None])[:, 0]
+    bound = 2 * d * 2.0 ** -24 * (h.double().abs() @ head.double().abs().T).max() + 16 * 2.0 ** -24 * (1 + nll.abs().max())
+    assert (sig.nll.cpu().double() - nll).abs().max() <= bound
