@@ -263,7 +263,10 @@ hipError_t forward_impl(const eat_ctx& h, const void* x, int32_t T, const float*
     if (e == hipSuccess)
         e = eat::launch_route(p, x, T, w_router, acc, ppl_trend, b.lpart, b.mask, b.k, b.gate, b.prob, stream);
     mark(EAT_STAGE_ROUTED);
-    if (e == hipSuccess)
+    Segments seg{};
+    if (T <= eat::kFusedTokens)
+        seg = Segments{b.mask, T, eat::mask_words(p.E), b.offsets, b.tok_idx, b.inv, expert_load_out};
+    else if (e == hipSuccess)
         e = eat::launch_permute(p, T, b.mask, b.offsets, b.tok_idx, b.inv, expert_load_out, stream);
     mark(EAT_STAGE_PERMUTED);
     const bool bf16 = p.expert_dtype == EAT_BF16;
@@ -271,13 +274,13 @@ hipError_t forward_impl(const eat_ctx& h, const void* x, int32_t T, const float*
         if (bf16)
             e = eat::launch_experts_bf16(p, T, w.rows, static_cast<const uint16_t*>(x),
                                          static_cast<const uint16_t*>(w1), static_cast<const uint16_t*>(w3),
-                                         static_cast<const uint16_t*>(w2), b.offsets, b.tok_idx,
+                                         static_cast<const uint16_t*>(w2), b.offsets, b.tok_idx, seg,
                                          static_cast<uint16_t*>(b.h), b.gu, b.yp, b.nrm2, up_splits_dev,
                                          down_splits_dev, stream, [&]() { mark(EAT_STAGE_UP); });
         else
             e = eat::launch_experts_f32(p, T, w.rows, static_cast<const float*>(x),
                                         static_cast<const float*>(w1), static_cast<const float*>(w3),
-                                        static_cast<const float*>(w2), b.offsets, b.tok_idx,
+                                        static_cast<const float*>(w2), b.offsets, b.tok_idx, seg,
                                         static_cast<float*>(b.h), b.yp, stream, [&]() { mark(EAT_STAGE_UP); });
     }
     mark(EAT_STAGE_DOWN);

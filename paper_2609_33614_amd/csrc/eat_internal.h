@@ -63,6 +63,21 @@ struct Buffers {
     unsigned* sync;          // kSyncWords words (see above)
 };
 
+// The token -> expert permutation of a call of at most kFusedTokens tokens is
+// worked out by the up/gate launch itself, from the selection masks
+// (eat_device.h): every workgroup the part it needs, and the launch also
+// writes the arrays that launch_permute writes for larger calls.  mask null:
+// they are already there.
+constexpr int kFusedTokens = 256;
+struct Segments {
+    const uint64_t* mask;    // [T][words]
+    int T, words;
+    int32_t* offsets;        // [E+1]
+    int32_t* tok_idx;        // [rows]
+    int32_t* inv;            // [T][E]
+    int32_t* expert_load;    // [E] or null
+};
+
 // ---- launchers (return hipGetLastError() after enqueueing) -------------
 
 hipError_t launch_reset_accounts(const eat_params_t& p, eat_accounts_t acc, hipStream_t s);
@@ -83,7 +98,8 @@ hipError_t launch_permute(const eat_params_t& p, int32_t T, const uint64_t* mask
 // fp32 weights and activations (small layers):
 hipError_t launch_experts_f32(const eat_params_t& p, int32_t T, int64_t rows_cap, const float* x,
                               const float* w1, const float* w3, const float* w2,
-                              const int32_t* offsets, const int32_t* tok_idx, float* h, float* yp, hipStream_t s,
+                              const int32_t* offsets, const int32_t* tok_idx, const Segments& seg, float* h,
+                              float* yp, hipStream_t s,
                               const std::function<void()>& between);
 
 // bf16 weights and activations: MFMA kernels.  Both projections choose
@@ -93,7 +109,7 @@ hipError_t launch_experts_f32(const eat_params_t& p, int32_t T, int64_t rows_cap
 // their partial sums of squares (norm_parts per row).
 hipError_t launch_experts_bf16(const eat_params_t& p, int32_t T, int64_t rows_cap,
                                const uint16_t* x, const uint16_t* w1, const uint16_t* w3,
-                               const uint16_t* w2, const int32_t* offsets, const int32_t* tok_idx,
+                               const uint16_t* w2, const int32_t* offsets, const int32_t* tok_idx, const Segments& seg,
                                uint16_t* h, float* gu, float* yp, float* nrm2, int32_t* up_splits_dev,
                                int32_t* down_splits_dev, hipStream_t s, const std::function<void()>& between);
 
@@ -198,7 +214,7 @@ constexpr int kMidChunkNs = 600, kTallChunkNs = 900;
 hipError_t launch_mid(bool gated, bool tall, const uint16_t* wa, const uint16_t* wb, const uint16_t* src,
                       const int32_t* gather, const int32_t* offsets, int groups, int nrows, int M, int K,
                       void* out, int64_t rows_cap, bool packed, int max_splits, int64_t split_stride,
-                      int32_t* splits_out, hipStream_t s);
+                      int32_t* splits_out, const Segments& seg, hipStream_t s);
 hipError_t launch_wide(bool gated, const uint16_t* wa, const uint16_t* wb, const uint16_t* src,
                        const int32_t* gather, const int32_t* offsets, int groups, int nrows, int M,
                        int K, void* out, int64_t rows_cap, bool packed, float* nrm2, hipStream_t s);

@@ -53,6 +53,7 @@ struct F32Args {
     int nrows;                 // rows of the single group when offsets is null
     int groups, M, K;
     float* out;                // [rows][M]
+    Segments seg;              // gated: set when this launch works out the permutation
 };
 
 constexpr int kF32Waves = 4, kF32Tok = 64;
@@ -62,11 +63,16 @@ __global__ __launch_bounds__(kF32Waves * kWave) void ffn_f32_kernel(F32Args a) {
     constexpr int NM = GATED ? 2 : 1, TT = kF32Tok / 16;
     __shared__ f32x4 red[kF32Waves][NM][TT][kWave];
     __shared__ int tstart[kMaxExperts + 1];
+    constexpr int NC = kFusedTokens / kWave;
+    __shared__ uint64_t cols[GATED ? kMaxExperts * NC : 1];
+    __shared__ int soff[GATED ? kMaxExperts + 1 : 1];
+    const bool fused = GATED && a.seg.mask != nullptr;
     const int lane = lane_id(), wave = threadIdx.x / kWave;
     const int i16 = lane & 15, kq = 4 * (lane >> 4);
     int ntiles;
     if (a.offsets) {
-        tile_starts(a.offsets, a.groups, kF32Tok, tstart);
+        if (fused) build_segments<kF32Waves, NC>(a.seg.mask, a.seg.T, a.groups, a.seg.words, cols, soff);
+        tile_starts(fused ? soff : a.offsets, a.groups, kF32Tok, tstart);
         ntiles = tstart[a.groups];
     } else {
         ntiles = (a.nrows + kF32Tok - 1) / kF32Tok;
@@ -78,8 +84,9 @@ __global__ __launch_bounds__(kF32Waves * kWave) void ffn_f32_kernel(F32Args a) {
         int e = 0, r0, n;
         if (a.offsets) {
             e = tile_group(tstart, a.groups, tile);
-            r0 = a.offsets[e] + (tile - tstart[e]) * kF32Tok;
-            n = min(kF32Tok, a.offsets[e + 1] - r0);
+            const int32_t* const off = fused ? soff : a.offsets;
+            r0 = off[e] + (tile - tstart[e]) * kF32Tok;
+            n = min(kF32Tok, off[e + 1] - r0);
         } else {
             r0 = tile * kF32Tok;
             n = min(kF32Tok, a.nrows - r0);
@@ -92,7 +99,8 @@ __global__ __launch_bounds__(kF32Waves * kWave) void ffn_f32_kernel(F32Args a) {
         for (int t = 0; t < TT; ++t) {
             // (rows past the tile read its first row; their columns are not stored)
             const int r = r0 + (16 * t + i16 < n ? 16 * t + i16 : 0);
-            xp[t] = a.src + static_cast<size_t>(a.gather ? a.gather[r] : r) * a.K + kq;
+            const int sr = fused ? nth_token<NC>(cols + e * NC, r - soff[e]) : a.gather ? a.gather[r] : r;
+            xp[t] = a.src + static_cast<size_t>(sr) * a.K + kq;
         }
         f32x4 acc[NM][TT];
 #pragma unroll
@@ -154,6 +162,9 @@ __global__ __launch_bounds__(kF32Waves * kWave) void ffn_f32_kernel(F32Args a) {
         }
         __syncthreads();
     }
+    if constexpr (GATED) {
+        if (fused) publish_segments<NC>(a.seg, a.groups, cols, soff);
+    }
 }
 
 template <bool GATED>
@@ -168,13 +179,13 @@ hipError_t launch_ffn_f32(const F32Args& a, int64_t max_tiles, hipStream_t s) {
 // expert when offsets is null).
 hipError_t launch_f32_pair(const float* x, const float* w1, const float* w3, const float* w2,
                            const int32_t* tok_idx, const int32_t* offsets, int nrows, int groups, int d, int F,
-                           int64_t max_tiles, float* h, float* yp, hipStream_t s,
+                           int64_t max_tiles, const Segments& seg, float* h, float* yp, hipStream_t s,
                            const std::function<void()>& between) {
     const hipError_t err =
-        launch_ffn_f32<true>(F32Args{w1, w3, x, tok_idx, offsets, nrows, groups, F, d, h}, max_tiles, s);
+        launch_ffn_f32<true>(F32Args{w1, w3, x, tok_idx, offsets, nrows, groups, F, d, h, seg}, max_tiles, s);
     if (err != hipSuccess) return err;
     if (between) between();
-    return launch_ffn_f32<false>(F32Args{w2, nullptr, h, nullptr, offsets, nrows, groups, d, F, yp}, max_tiles, s);
+    return launch_ffn_f32<false>(F32Args{w2, nullptr, h, nullptr, offsets, nrows, groups, d, F, yp, {}}, max_tiles, s);
 }
 
 // ------------------------------------------------------- bf16 streaming --
@@ -249,6 +260,7 @@ struct StreamArgs {
     float* out2;               // gated: fp32 U partials [split][rows][M]
     uint16_t* h;               // gated: bf16 H [rows][M] (written here when one slice is taken)
     int kin;                   // gated: reduction groups per workgroup (2, or 1 when 0 or 1)
+    Segments seg;              // gated: set when this launch works out the permutation
     int narrow;                // host only: plain kernels keep 4-wave workgroups (more,
                                // smaller work items) instead of 8
 };
@@ -356,6 +368,12 @@ __attribute__((amdgpu_waves_per_eu((KIN == 2 && NSUB >= 8) ? 2 : 3, 8))) void st
     };
     __shared__ int tstart[kMaxExperts + 1];
     __shared__ int used_groups;
+    // tiles of up to 64 tokens serve calls of up to 64
+    constexpr int NC = NSUB <= 4 ? 1 : kFusedTokens / kWave;
+    __shared__ uint64_t cols[GATED ? kMaxExperts * NC : 1];
+    __shared__ int soff[GATED ? kMaxExperts + 1 : 1];
+    constexpr bool kFused = GATED && 16 * NSUB <= kFusedTokens / 4;   // always (routed rows)
+    const bool fused = kFused ? a.offsets != nullptr : GATED && a.seg.mask != nullptr;
     const int lane = lane_id();
     // reduction group (uniform over the wave), the wave's place in it and
     // the thread's
@@ -365,7 +383,8 @@ __attribute__((amdgpu_waves_per_eu((KIN == 2 && NSUB >= 8) ? 2 : 3, 8))) void st
 
     int ntiles, used = 1;
     if (a.offsets) {
-        tile_starts<true>(a.offsets, a.groups, BN, tstart, &used_groups);
+        if (fused) build_segments<WPB * KIN, NC>(a.seg.mask, a.seg.T, a.groups, a.seg.words, cols, soff);
+        tile_starts<true>(fused ? soff : a.offsets, a.groups, BN, tstart, &used_groups);
         ntiles = tstart[a.groups];
         used = used_groups;
     } else {
@@ -404,8 +423,17 @@ __attribute__((amdgpu_waves_per_eu((KIN == 2 && NSUB >= 8) ? 2 : 3, 8))) void st
             int e = 0, r0, n;
             if (a.offsets) {
                 e = tile_group(tstart, a.groups, tile);
-                r0 = a.offsets[e] + (tile - tstart[e]) * BN;
-                n = min(BN, a.offsets[e + 1] - r0);
+                if (fused) {
+                    r0 = soff[e] + (tile - tstart[e]) * BN;
+                    n = min(BN, soff[e + 1] - r0);
+                    // uniform: keep the item in scalar registers
+                    e = __builtin_amdgcn_readfirstlane(e);
+                    r0 = __builtin_amdgcn_readfirstlane(r0);
+                    n = __builtin_amdgcn_readfirstlane(n);
+                } else {
+                    r0 = a.offsets[e] + (tile - tstart[e]) * BN;
+                    n = min(BN, a.offsets[e + 1] - r0);
+                }
             } else {
                 r0 = tile * BN;
                 n = min(BN, a.nrows - r0);
@@ -428,7 +456,9 @@ __attribute__((amdgpu_waves_per_eu((KIN == 2 && NSUB >= 8) ? 2 : 3, 8))) void st
                 const int v = tid + NT * r;
                 const int row = v / VPR, col = v % VPR;
                 xon[r] = row < n;
-                const int srow = xon[r] ? (a.gather ? a.gather[r0 + row] : r0 + row) : 0;
+                const int srow = !xon[r] ? 0
+                                 : fused ? nth_token<NC>(cols + e * NC, r0 - soff[e] + row)
+                                         : (!kFused && a.gather ? a.gather[r0 + row] : r0 + row);
                 xsrc[r] = a.src + static_cast<size_t>(srow) * a.K + kbeg + 8 * col;
                 xdst[r] = row * LDS_ROW + 8 * col;
             }
@@ -655,6 +685,9 @@ __attribute__((amdgpu_waves_per_eu((KIN == 2 && NSUB >= 8) ? 2 : 3, 8))) void st
     } else {
         run(std::true_type{});
     }
+    if constexpr (GATED) {
+        if (fused) publish_segments<NC>(a.seg, a.groups, cols, soff);
+    }
 }
 
 // out[i] = sum_s part[s][i] (float4 elements, slices added in slice order).
@@ -793,6 +826,8 @@ template <bool GATED, int NSUB, int KS, int WPB, bool PACKED, int KIN>
 hipError_t launch_stream_wk(const StreamArgs& a, int64_t max_tiles, hipStream_t s) {
     const int64_t items = max_tiles * a.splits * (a.M / (16 * WPB));
     if (items >= (int64_t{1} << 31)) return hipErrorInvalidValue;
+    // routed gated tiles of up to 64 tokens take their rows from the masks
+    if (GATED && NSUB <= 4 && a.offsets && !a.seg.mask) return hipErrorInvalidValue;
     int64_t blocks = std::max<int64_t>(1, std::min(items, stream_resident<GATED, NSUB, KS, WPB, PACKED, KIN>()));
     stream_kernel<GATED, NSUB, KS, WPB, PACKED, KIN>
         <<<dim3(static_cast<unsigned>(blocks)), dim3(WPB * 64 * KIN), 0, s>>>(a);
@@ -1021,29 +1056,29 @@ int head_splits(int M, int K, int32_t T) {
 hipError_t launch_head_bf16(const uint16_t* src, int32_t T, const uint16_t* w, int M, int K, float* out,
                             int splits, int64_t split_stride, hipStream_t s) {
     if (head_mid(M, K, T))
-        return launch_mid(false, T > 128, w, nullptr, src, nullptr, nullptr, 1, T, M, K, out, T, false, 1, 0, nullptr, s);
+        return launch_mid(false, T > 128, w, nullptr, src, nullptr, nullptr, 1, T, M, K, out, T, false, 1, 0, nullptr, {}, s);
     return launch_dense_bf16(src, T, w, M, K, out, splits, split_stride, s);
 }
 
 hipError_t launch_experts_f32(const eat_params_t& p, int32_t T, int64_t rows_cap, const float* x,
                               const float* w1, const float* w3, const float* w2,
-                              const int32_t* offsets, const int32_t* tok_idx, float* h, float* yp, hipStream_t s,
-                              const std::function<void()>& between) {
+                              const int32_t* offsets, const int32_t* tok_idx, const Segments& seg, float* h,
+                              float* yp, hipStream_t s, const std::function<void()>& between) {
     const int64_t per_expert = (T + kF32Tok - 1) / kF32Tok;
     const int64_t tiles = std::min<int64_t>({rows_cap, per_expert * p.E, (rows_cap + kF32Tok - 1) / kF32Tok + p.E});
-    return launch_f32_pair(x, w1, w3, w2, tok_idx, offsets, 0, p.E, p.d_model, p.d_ffn, tiles, h, yp, s, between);
+    return launch_f32_pair(x, w1, w3, w2, tok_idx, offsets, 0, p.E, p.d_model, p.d_ffn, tiles, seg, h, yp, s, between);
 }
 
 hipError_t launch_shared_f32(const eat_params_t& p, int32_t T, const float* x, const float* ws1,
                              const float* ws3, const float* ws2, float* hs, float* ys,
                              hipStream_t s) {
     return launch_f32_pair(x, ws1, ws3, ws2, nullptr, nullptr, T, 1, p.d_model, p.d_shared,
-                           (T + kF32Tok - 1) / kF32Tok, hs, ys, s, nullptr);
+                           (T + kF32Tok - 1) / kF32Tok, {}, hs, ys, s, nullptr);
 }
 
 hipError_t launch_experts_bf16(const eat_params_t& p, int32_t T, int64_t rows_cap, const uint16_t* x,
                                const uint16_t* w1, const uint16_t* w3, const uint16_t* w2,
-                               const int32_t* offsets, const int32_t* tok_idx, uint16_t* h,
+                               const int32_t* offsets, const int32_t* tok_idx, const Segments& seg, uint16_t* h,
                                float* gu, float* yp, float* nrm2, int32_t* up_splits_dev, int32_t* down_splits_dev,
                                hipStream_t s, const std::function<void()>& between) {
     const int nsub = pick_nsub(T);
@@ -1066,11 +1101,11 @@ hipError_t launch_experts_bf16(const eat_params_t& p, int32_t T, int64_t rows_ca
         const bool tall = mid_tall(std::min<int64_t>(p.mode == EAT_MODE_EAT && p.cs_mode == 0 ? p.top_k : p.E, assign),
                                    assign, p.d_ffn);
         hipError_t err = launch_mid(true, tall, w1, w3, x, tok_idx, offsets, p.E, 0, p.d_ffn, p.d_model, h, rows_cap, packed,
-                                    1, 0, nullptr, s);
+                                    1, 0, nullptr, seg, s);
         if (err != hipSuccess) return err;
         if (between) between();
         return launch_mid(false, tall, w2, nullptr, h, nullptr, offsets, p.E, 0, p.d_model, p.d_ffn, yp, rows_cap, packed,
-                          down_splits(p, T), rows_cap * p.d_model, down_splits_dev, s);
+                          down_splits(p, T), rows_cap * p.d_model, down_splits_dev, {}, s);
     }
     // both projections take their slices on the device, from the tiles in use
     const int usplits = up_splits(p, T);
@@ -1084,6 +1119,7 @@ hipError_t launch_experts_bf16(const eat_params_t& p, int32_t T, int64_t rows_ca
     up.out2 = gu + usplits * up.split_stride;
     up.h = h;
     up.splits_out = up_splits_dev;
+    up.seg = seg;
     hipError_t err = launch_stream<true>(up, nsub, max_tiles, packed, s);
     if (err != hipSuccess) return err;
     if (usplits > 1) {
@@ -1163,10 +1199,10 @@ hipError_t launch_shared_bf16(const eat_params_t& p, int32_t T, const uint16_t* 
     if (shared_mid(p, T)) {
         const bool tall = mid_tall(1, T, p.d_shared);
         hipError_t err = launch_mid(true, tall, ws1, ws3, x, nullptr, nullptr, 1, T, p.d_shared, p.d_model, hs, T,
-                                    packed, 1, 0, nullptr, s);
+                                    packed, 1, 0, nullptr, {}, s);
         if (err != hipSuccess) return err;
         err = launch_mid(false, tall, ws2, nullptr, hs, nullptr, nullptr, 1, T, p.d_model, p.d_shared, dout, T, packed,
-                         splits, stride, nullptr, s);
+                         splits, stride, nullptr, {}, s);
         return err == hipSuccess ? sum() : err;
     }
     const int nsub = pick_nsub(T);

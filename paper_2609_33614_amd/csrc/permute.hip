@@ -1,4 +1,5 @@
-// Token -> expert permutation (gfx950).
+// Token -> expert permutation (gfx950) of calls of more than kFusedTokens
+// tokens (smaller ones work it out in the up/gate launch, eat_device.h).
 //
 // The selected (token, expert) pairs are laid out expert-major: expert e
 // owns rows [offsets[e], offsets[e+1]), and inside that range its tokens
@@ -18,9 +19,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 
-// PRE: chunks of kThreads tokens whose mask words are loaded together (1
-// for calls of at most kThreads tokens, where more would only add loads).
-template <int PRE>
 __global__ __launch_bounds__(kThreads) void permute_kernel(
     const uint64_t* __restrict__ mask, int T, int E, int W, int32_t* __restrict__ offsets,
     int32_t* __restrict__ tok_idx, int32_t* __restrict__ inv, int32_t* __restrict__ expert_load) {
@@ -36,7 +34,7 @@ __global__ __launch_bounds__(kThreads) void permute_kernel(
     // the chunks' mask words before using any (one memory round trip per
     // kPre chunks, not per chunk; tokens past T read token 0's word and are
     // off).
-    constexpr int kPre = PRE;
+    constexpr int kPre = 16;
     auto load_words = [&](int base0, int word, uint64_t (&mw)[kPre]) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < kPre; ++i) {
@@ -112,12 +110,8 @@ __global__ __launch_bounds__(kThreads) void permute_kernel(
 
 hipError_t launch_permute(const eat_params_t& p, int32_t T, const uint64_t* mask, int32_t* offsets,
                           int32_t* tok_idx, int32_t* inv, int32_t* expert_load, hipStream_t s) {
-    if (T <= kThreads)
-        permute_kernel<1><<<dim3(p.E), dim3(kThreads), 0, s>>>(mask, T, p.E, mask_words(p.E), offsets, tok_idx,
-                                                               inv, expert_load);
-    else
-        permute_kernel<16><<<dim3(p.E), dim3(kThreads), 0, s>>>(mask, T, p.E, mask_words(p.E), offsets, tok_idx,
-                                                                inv, expert_load);
+    permute_kernel<<<dim3(p.E), dim3(kThreads), 0, s>>>(mask, T, p.E, mask_words(p.E), offsets, tok_idx, inv,
+                                                        expert_load);
     return hipGetLastError();
 }
 

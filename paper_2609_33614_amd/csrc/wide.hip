@@ -88,6 +88,7 @@ struct WideArgs {
     int max_splits;            // plain fp32: most slices of the reduction dimension (tile_split)
     int64_t split_stride;      // elements between slices of out
     int32_t* splits_out;       // the slices taken, written by workgroup 0 (or null)
+    Segments seg;              // gated: set when this launch works out the permutation
 };
 
 // Byte offset of 16-byte vector v of row r in a region of kRB-byte rows.
@@ -253,11 +254,21 @@ __global__ __launch_bounds__(C::kThreads) void wide_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint8_t ring[C::STAGES * C::kStage];
     __shared__ int tstart[kMaxExperts + 1];
     __shared__ int soff[kMaxExperts + 1];     // the segment offsets, read per item without a memory wait
+    // (the prefill tile never serves calls that small)
+    constexpr bool kFuse = GATED && C::TM * C::NW < 256 * 256;
+    constexpr int NC = kFusedTokens / kWave;
+    __shared__ uint64_t cols[kFuse ? kMaxExperts * NC : 1];
+    const bool fused = kFuse && a.seg.mask != nullptr;
 
     int ntiles;
     if (a.offsets) {
-        for (int g = threadIdx.x; g <= a.groups; g += C::kThreads) soff[g] = a.offsets[g];
-        tile_starts(a.offsets, a.groups, TM, tstart);    // ends with a barrier
+        if (fused) {
+            build_segments<C::kWaves, NC>(a.seg.mask, a.seg.T, a.groups, a.seg.words, cols, soff);
+            tile_starts(soff, a.groups, TM, tstart);     // ends with a barrier
+        } else {
+            for (int g = threadIdx.x; g <= a.groups; g += C::kThreads) soff[g] = a.offsets[g];
+            tile_starts(a.offsets, a.groups, TM, tstart);
+        }
         ntiles = tstart[a.groups];
     } else {
         ntiles = (a.nrows + TM - 1) / TM;
@@ -317,7 +328,25 @@ __global__ __launch_bounds__(C::kThreads) void wide_kernel(WideArgs a) {
     };
 
     int wid = wbeg + slot;
-    if (wid >= wend) return;                  // uniform over the workgroup
+    if (wid >= wend) {                        // uniform over the workgroup
+        if constexpr (kFuse) {
+            if (fused) publish_segments<NC>(a.seg, a.groups, cols, soff);
+        }
+        return;
+    }
+    auto source_rows = [&](const Item& it, int (&srow)[C::kBT]) __attribute__((always_inline)) {
+        if constexpr (kFuse) {
+            if (fused) {
+#pragma unroll
+                for (int j = 0; j < C::kBT; ++j) {
+                    const int r = kRPB * (static_cast<int>(threadIdx.x) / kWave + C::kWaves * j) + lane_id() / kVPR;
+                    srow[j] = nth_token<NC>(cols + it.e * NC, it.r0 - soff[it.e] + (r < it.n ? r : 0));
+                }
+                return;
+            }
+        }
+        token_rows<C>(a, it, srow);
+    };
 
     const int lane = lane_id(), wave = threadIdx.x / kWave;
     const int l32 = lane & 31, lh = lane >> 5;
@@ -341,7 +370,7 @@ __global__ __launch_bounds__(C::kThreads) void wide_kernel(WideArgs a) {
     // refill wait behind the item's output stores.
     Item cur = item_at(wid);
     int srow[C::kBT];
-    token_rows<C>(a, cur, srow);
+    source_rows(cur, srow);
     ItemLoads<C> ld = item_loads<C, GATED, PACKED>(a, cur, cur.sp * ks, srow);
 #pragma unroll
     for (int c = 0; c < C::kP; ++c)
@@ -359,7 +388,7 @@ __global__ __launch_bounds__(C::kThreads) void wide_kernel(WideArgs a) {
         Item nxt = cur;
         if (more) {
             nxt = item_at(nwid);
-            token_rows<C>(a, nxt, srow);
+            source_rows(nxt, srow);
         }
         // this wave's token group holds rows of the expert
         const bool active = brow < cur.n;
@@ -500,6 +529,9 @@ __global__ __launch_bounds__(C::kThreads) void wide_kernel(WideArgs a) {
         cur = nxt;
         wid = nwid;
     }
+    if constexpr (kFuse) {
+        if (fused) publish_segments<NC>(a.seg, a.groups, cols, soff);
+    }
 }
 
 }  // namespace
@@ -563,7 +595,7 @@ hipError_t launch_wide(bool gated, const uint16_t* wa, const uint16_t* wb, const
                        const int32_t* gather, const int32_t* offsets, int groups, int nrows, int M, int K,
                        void* out, int64_t rows_cap, bool packed, float* nrm2, hipStream_t s) {
     if (nrm2 && gated) return hipErrorInvalidValue;
-    WideArgs a{wa, wb, src, gather, offsets, groups, nrows, M, K, out, nrm2, geometry().xcds, 1, 0, nullptr};
+    WideArgs a{wa, wb, src, gather, offsets, groups, nrows, M, K, out, nrm2, geometry().xcds, 1, 0, nullptr, {}};
     const int64_t work =
         most_tiles(offsets, rows_cap, groups, nrows, Wide::TM) * (M / (gated ? Wide::NW / 2 : Wide::NW));
     if (gated) return packed ? launch_tile<Wide, true, true, false>(a, work, s) : launch_tile<Wide, true, false, false>(a, work, s);
@@ -587,9 +619,10 @@ hipError_t launch_mid_t(bool gated, WideArgs& a, int64_t rows_cap, bool packed, 
 hipError_t launch_mid(bool gated, bool tall, const uint16_t* wa, const uint16_t* wb, const uint16_t* src,
                       const int32_t* gather, const int32_t* offsets, int groups, int nrows, int M, int K,
                       void* out, int64_t rows_cap, bool packed, int max_splits, int64_t split_stride,
-                      int32_t* splits_out, hipStream_t s) {
+                      int32_t* splits_out, const Segments& seg, hipStream_t s) {
+    if (seg.mask && !gated) return hipErrorInvalidValue;
     WideArgs a{wa, wb, src, gather, offsets, groups, nrows, M, K, out, nullptr, geometry().xcds,
-               max_splits, split_stride, splits_out};
+               max_splits, split_stride, splits_out, seg};
     return tall ? launch_mid_t<Tall>(gated, a, rows_cap, packed, s) : launch_mid_t<Mid>(gated, a, rows_cap, packed, s);
 }
 
