@@ -478,8 +478,7 @@ eat_status_t eat_pack_weights(const void* src, int32_t groups, int32_t M, int32_
 eat_status_t eat_ppl_workspace_size(int32_t S, int32_t d, int32_t V, size_t* bytes) {
     if (!bytes || S < 0 || S > kMaxTokens || d < 64 || d % 64 || V < 64 || V % 64) return EAT_ERR_INVALID_ARG;
     if (static_cast<int64_t>(d) * V >= (int64_t{1} << 31)) return EAT_ERR_INVALID_ARG;
-    *bytes = align256(static_cast<size_t>(eat::head_splits(V, d, S)) * S * V * 4) +
-             align256(static_cast<size_t>(S) * eat::ppl_chunks(V) * 8);
+    *bytes = align256(static_cast<size_t>(eat::head_splits(V, d, S)) * S * V * 4);
     return EAT_OK;
 }
 
@@ -511,10 +510,7 @@ eat_status_t eat_ppl_trend(const void* h, int32_t S, int32_t d, const void* w_vo
     hipError_t e = eat::launch_head_bf16(static_cast<const uint16_t*>(h), S, static_cast<const uint16_t*>(w_vocab),
                                          V, d, z, splits, stride, stream);
     if (e == hipSuccess)
-        e = eat::launch_ppl(z, splits, stride, S, V, target, nll_sum, count, ppl_prev, trend_out, nll_out,
-                            reinterpret_cast<float2*>(static_cast<char*>(ws) +
-                                                      align256(static_cast<size_t>(splits) * S * V * 4)),
-                            stream);
+        e = eat::launch_ppl(z, splits, stride, S, V, target, nll_sum, count, ppl_prev, trend_out, nll_out, stream);
     return e == hipSuccess ? EAT_OK : EAT_ERR_HIP;
 }
 

@@ -229,8 +229,7 @@ hipError_t launch_pack(const uint16_t* src, int32_t groups, int32_t M, int32_t K
 // launch_ppl_reset zeroes the state.
 hipError_t launch_ppl(const float* z, int splits, int64_t stride, int32_t S, int V, const int32_t* target,
                       double* nll_sum, int32_t* count, double* ppl_prev, int8_t* trend, float* nll_out,
-                      float2* part, hipStream_t s);
-int ppl_chunks(int V);                 // (max, sum) pairs per row in `part`
+                      hipStream_t s);
 hipError_t launch_ppl_reset(int32_t S, double* nll_sum, int32_t* count, double* ppl_prev, hipStream_t s);
 
 // Forward entry points (api.cpp): host-side argument checks, and the

@@ -3,17 +3,15 @@
 //
 // The LM-head projection z = h W_V^T runs on the MFMA tiles (wide.hip) into
 // fp32 rows, or on the streaming kernel (expert.hip) where the reduction is too
-// short for them (up to two slices of it, added in order here).  ppl_chunk_kernel folds
-// each of up to 16 vocabulary chunks of a row into an online logsumexp
-// pair (running max, sum of exp(z - max)) in one pass; ppl_finish_kernel
-// merges a row's chunks in order and forms NLL = logsumexp - z[target] and
-// the sequence's running state in fp64: sum of NLL, token count, perplexity
-// exp(sum / count) and the trend (+1 rose since the previous token, -1 did
-// not, 0 first token).  Every merge has a fixed order, so results are
-// bit-reproducible.
+// short for them (up to two slices of it, added in order here).
+// ppl_kernel, one workgroup per sequence, folds the row into an online
+// logsumexp pair (running max, sum of exp(z - max)): a thread's values a block
+// at a time, then the wave by butterfly, then the waves in order; its first
+// thread forms NLL = logsumexp - z[target] and the sequence's running state in
+// fp64: sum of NLL, token count, perplexity exp(sum / count) and the trend (+1
+// rose since the previous token, -1 did not, 0 first token).  Every merge has a
+// fixed order, so results are bit-reproducible.
 #include <math.h>
-
-#include <algorithm>
 
 #include "eat_device.h"
 #include "eat_internal.h"
@@ -21,9 +19,10 @@
 namespace eat {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kPplChunks = 16;            // vocabulary chunks per row in the logsumexp pass
+// float4s a thread has in flight: a row of 32000 logits is one block of loads
+constexpr int kVec = 8;
 
 // online logsumexp pair (m, s): the running max and sum of exp(z - m)
 struct Lse {
@@ -43,20 +42,46 @@ __device__ __forceinline__ float logit(const float* row, int splits, int64_t str
     return v;
 }
 
-// grid (S, chunks): each workgroup folds one chunk of a row into an (m, s)
-// pair in one pass; lanes by stride, then the wave by butterfly, then the
-// waves in order.
-__global__ __launch_bounds__(kThreads) void ppl_chunk_kernel(const float* __restrict__ z, int splits, int64_t stride,
-                                                             int V, int chunk, float2* __restrict__ part) {
+// exp(v - m) of a value of a block with maximum m (the maximum itself counts
+// 1 also where it is infinite)
+__device__ __forceinline__ float term(float v, float m) { return v == m ? 1.f : expf(v - m); }
+
+// One workgroup per sequence: 128 KB of logits are a latency and a few us for
+// a CU, less than the launch that a split over more workgroups needs to merge
+// its parts (16 chunks a row, 256 threads each, and a finishing launch: 14.4 us
+// at 64 x 32000 against 6.5).
+__global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__ z, int splits, int64_t stride, int V,
+                                                       const int32_t* __restrict__ target, double* nll_sum,
+                                                       int32_t* count, double* ppl_prev, int8_t* trend,
+                                                       float* nll_out) {
     __shared__ Lse red[kWaves];
-    const int s = blockIdx.x, c = blockIdx.y;
+    const int s = blockIdx.x;
     const float* row = z + static_cast<size_t>(s) * V;
-    const int j0 = c * chunk, j1 = min(V, j0 + chunk);
     Lse a{-INFINITY, 0.f};
-    for (int j = j0 + threadIdx.x; j < j1; j += kThreads) {
-        const float v = logit(row, splits, stride, j);
-        if (v > a.m) { a.s = a.s * expf(a.m - v) + 1.f; a.m = v; }
-        else a.s += expf(v - a.m);
+    // (V is a multiple of 64)
+    for (int j0 = 4 * threadIdx.x; j0 < V; j0 += 4 * kThreads * kVec) {
+        float4 v[kVec];
+#pragma unroll
+        for (int i = 0; i < kVec; ++i) {
+            const int j = j0 + 4 * kThreads * i;
+            v[i] = *reinterpret_cast<const float4*>(row + (j < V ? j : j0));
+        }
+        for (int sp = 1; sp < splits; ++sp)
+#pragma unroll
+            for (int i = 0; i < kVec; ++i) {
+                const int j = j0 + 4 * kThreads * i;
+                const float4 q = *reinterpret_cast<const float4*>(row + sp * stride + (j < V ? j : j0));
+                v[i].x += q.x; v[i].y += q.y; v[i].z += q.z; v[i].w += q.w;
+            }
+        Lse b{-INFINITY, 0.f};
+#pragma unroll
+        for (int i = 0; i < kVec; ++i)
+            if (j0 + 4 * kThreads * i < V) b.m = fmaxf(b.m, fmaxf(fmaxf(v[i].x, v[i].y), fmaxf(v[i].z, v[i].w)));
+#pragma unroll
+        for (int i = 0; i < kVec; ++i)
+            if (j0 + 4 * kThreads * i < V)
+                b.s += (term(v[i].x, b.m) + term(v[i].y, b.m)) + (term(v[i].z, b.m) + term(v[i].w, b.m));
+        a = lse_merge(a, b);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -70,28 +95,11 @@ __global__ __launch_bounds__(kThreads) void ppl_chunk_kernel(const float* __rest
     Lse t = red[0];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) t = lse_merge(t, red[w]);
-    part[static_cast<size_t>(s) * gridDim.y + c] = make_float2(t.m, t.s);
-}
-
-// one thread per sequence: chunks merged in order, NLL, running state, trend
-__global__ __launch_bounds__(kThreads) void ppl_finish_kernel(const float* __restrict__ z, int splits,
-                                                              int64_t stride, int S, int V, int chunks,
-                                                              const float2* __restrict__ part,
-                                                              const int32_t* __restrict__ target, double* nll_sum,
-                                                              int32_t* count, double* ppl_prev, int8_t* trend,
-                                                              float* nll_out) {
-    const int s = blockIdx.x * kThreads + threadIdx.x;
-    if (s >= S) return;
-    Lse t{-INFINITY, 0.f};
-    for (int c = 0; c < chunks; ++c) {
-        const float2 q = part[static_cast<size_t>(s) * chunks + c];
-        t = lse_merge(t, Lse{q.x, q.y});
-    }
     const int y = target[s];
     double nll = NAN;
     if (y >= 0 && y < V)
         nll = static_cast<double>(t.m) + log(static_cast<double>(t.s)) -
-              static_cast<double>(logit(z + static_cast<size_t>(s) * V, splits, stride, y));
+              static_cast<double>(logit(row, splits, stride, y));
     const double sum = nll_sum[s] + nll;
     const int32_t n = count[s] + 1;
     const double ppl = exp(sum / n);
@@ -110,18 +118,10 @@ __global__ __launch_bounds__(kThreads) void ppl_reset_kernel(int S, double* nll_
 
 }  // namespace
 
-int ppl_chunks(int V) { return std::min(kPplChunks, (V + kThreads - 1) / kThreads); }
-
 hipError_t launch_ppl(const float* z, int splits, int64_t stride, int32_t S, int V, const int32_t* target,
                       double* nll_sum, int32_t* count, double* ppl_prev, int8_t* trend, float* nll_out,
-                      float2* part, hipStream_t s) {
-    const int chunks = ppl_chunks(V);
-    const int chunk = (V + chunks - 1) / chunks;
-    ppl_chunk_kernel<<<dim3(S, chunks), kThreads, 0, s>>>(z, splits, stride, V, chunk, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    ppl_finish_kernel<<<(S + kThreads - 1) / kThreads, kThreads, 0, s>>>(z, splits, stride, S, V, chunks, part, target,
-                                                                         nll_sum, count, ppl_prev, trend, nll_out);
+                      hipStream_t s) {
+    ppl_kernel<<<S, kThreads, 0, s>>>(z, splits, stride, V, target, nll_sum, count, ppl_prev, trend, nll_out);
     return hipGetLastError();
 }
 
