@@ -299,15 +299,15 @@ hipError_t forward_impl(const eat_ctx& h, const void* x, int32_t T, const float*
     // the down projection's slices: chosen on the device when it could take several
     const int32_t* splits_dev = bf16 && w.splits > 1 ? down_splits_dev : nullptr;
     const bool rows16 = bf16 && eat::rows_bf16(p, T);
+    // (the hidden rows, at least 128 bytes each, are free once the down projection has read them)
+    float2* const stats = rows16 ? static_cast<float2*>(b.h) : nullptr;
     if (e == hipSuccess)
         e = eat::launch_combine(p, T, b.mask, b.gate, b.inv, b.yp, shared ? b.ys : nullptr, residual, y, b.nrm2,
-                                w.splits, w.rows * p.d_model, splits_dev, rows16, stream);
+                                w.splits, w.rows * p.d_model, splits_dev, rows16, b.prob, stats, stream);
     mark(EAT_STAGE_COMBINED);
     if (defer) *defer = AccountJob{};
     if (e == hipSuccess && p.mode == EAT_MODE_EAT) {
-        // (the prefill combine leaves a row's sum of squares in its first partial)
-        const int parts = eat::norm_parts(p, T);
-        const AccountJob job{b.offsets, b.tok_idx, b.prob, b.nrm2, rows16 ? 1 : parts, parts, p.E, p.alpha, acc};
+        const AccountJob job{b.offsets, b.tok_idx, b.prob, b.nrm2, stats, eat::norm_parts(p, T), p.E, p.alpha, acc};
         if (defer) *defer = job;
         else e = eat::launch_update_accounts(job, T, stream);
     }

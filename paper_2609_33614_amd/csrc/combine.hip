@@ -19,7 +19,7 @@
 //   N += n_e,  P_total += sum of the rows' router probabilities,
 //   C_s = (1 - alpha) C_s + alpha * mean row norm,
 // each row norm being sqrt of its partial sums of squares (the combine's
-// slices added in order, or the total the prefill combine leaves).
+// slices added in order, or the prefill combine's totals).
 // (Doing it in the combine's last workgroup to finish instead of a kernel of
 // its own needs a device-wide release in every combine workgroup, an L2
 // write-back on this part: measured slower at every decode size.)
@@ -43,7 +43,9 @@ struct CombineArgs {
     const float* ys;           // [T][d] shared output or null
     const uint16_t* res;       // [T][d] bf16 residual rows added to y, or null
     void* y;
-    float* nrm2;               // [rows_cap][nchunk] partial sums of squares, or null: not wanted
+    float* nrm2;               // [rows_cap][nchunk] partial sums of squares
+    const float* prob;         // combine_rows16_kernel: [T][E] router probabilities, and
+    float2* stats;             // [rows_cap] (sum of squares, probability)
     int64_t split_stride;
     int splits, T, E, d, nchunk, words;
 };
@@ -184,13 +186,15 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(CombineArgs a) {
 // per (token, 2048-element slice of d), 8 elements a thread (16-byte loads),
 // every row of a batch of the token's experts loaded before the first is
 // added; the same order of additions as combine_kernel.  y is bf16.
-// For the account update (a.nrm2 set) the token's first workgroup also adds up
+// For the account update (STATS) the token's first workgroup also adds up
 // each of its rows' nchunk partial sums of squares, one wave a row and a
-// lane per partial, and leaves the total in the row's first one: the update
-// then reads one value a row.  (It used to read all 64 itself, one workgroup
-// per expert: 144 us of a 8192-token call whose tokens share 4 experts, now
-// under 10.)
+// lane per partial, and writes the total and the row's router probability
+// side by side in row order: the update's one workgroup per expert then reads
+// 8 contiguous bytes a row.  8192 tokens that share 4 experts: 144 us when it
+// read all 64 partials and gathered the probabilities itself, 33 when it read one
+// partial a row (a 128-byte line each, as is every gathered probability), 7 now.
 constexpr int kRowVec = 8;
+template <bool STATS>
 __global__ __launch_bounds__(kThreads) void combine_rows16_kernel(CombineArgs a) {
     const int t = blockIdx.x;
     const int j = blockIdx.y * kThreads + threadIdx.x;     // 8-element group of the row
@@ -219,16 +223,16 @@ __global__ __launch_bounds__(kThreads) void combine_rows16_kernel(CombineArgs a)
     int w = 0;
     uint64_t rest = mt[0];
     for (;;) {
-        int rows[kBatch];
+        int rows[kBatch], es[kBatch];
         float gs[kBatch];
         int nb = 0;
 #pragma unroll
         for (int b = 0; b < kBatch; ++b) {
             while (rest == 0 && w + 1 < a.words) rest = mt[++w];
-            rows[b] = 0;
+            rows[b] = es[b] = 0;
             gs[b] = 0.f;
             if (rest != 0) {
-                const int e = 64 * w + __builtin_ctzll(rest);
+                const int e = es[b] = 64 * w + __builtin_ctzll(rest);
                 rest &= rest - 1;
                 rows[b] = a.inv[static_cast<size_t>(t) * a.E + e];
                 gs[b] = a.gate[static_cast<size_t>(t) * a.E + e];
@@ -236,23 +240,24 @@ __global__ __launch_bounds__(kThreads) void combine_rows16_kernel(CombineArgs a)
             }
         }
         if (nb == 0) break;
-        if (a.nrm2 && blockIdx.y == 0) {      // uniform
-            const int lane = lane_id(), wave = threadIdx.x / kWave;
-#pragma unroll
-            for (int b = 0; b < kBatch; ++b) {
-                if (b >= nb || b % kWaves != wave) continue;
-                float* const rp = a.nrm2 + static_cast<int64_t>(rows[b]) * a.nchunk;
-                float ss = 0.f;
-                for (int c = lane; c < a.nchunk; c += kWave) ss += rp[c];
-                ss = wave_sum(ss);            // every lane's loads are done: the total may take the first's place
-                if (lane == 0) rp[0] = ss;
-            }
-        }
         // (rows past nb read row 0, unused)
         uint4 q[kBatch];
 #pragma unroll
         for (int b = 0; b < kBatch; ++b)
             q[b] = *reinterpret_cast<const uint4*>(yph + static_cast<int64_t>(rows[b]) * a.d + kRowVec * jc);
+        if (STATS && blockIdx.y == 0) {       // uniform
+            const int lane = lane_id(), wave = threadIdx.x / kWave;
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                if (b >= nb || b % kWaves != wave) continue;
+                const float* const rp = a.nrm2 + static_cast<int64_t>(rows[b]) * a.nchunk;
+                const float p = a.prob[static_cast<size_t>(t) * a.E + es[b]];
+                float ss = 0.f;
+                for (int c = lane; c < a.nchunk; c += kWave) ss += rp[c];
+                ss = wave_sum(ss);
+                if (lane == 0) a.stats[rows[b]] = make_float2(ss, p);
+            }
+        }
 #pragma unroll
         for (int b = 0; b < kBatch; ++b) {
             if (b >= nb) break;
@@ -295,7 +300,8 @@ __device__ __forceinline__ void account_update(const AccountJob& j, int e) {
     const int32_t* __restrict__ tok_idx = j.tok_idx;
     const float* __restrict__ prob = j.prob;
     const float* __restrict__ nrm2 = j.nrm2;
-    const int parts = j.parts, stride = j.stride, E = j.experts;
+    const float2* __restrict__ stats = j.stats;
+    const int parts = j.parts, E = j.experts;
     const float alpha = j.alpha;
     int64_t* __restrict__ n = j.acc.n;
     float* __restrict__ p_total = j.acc.p_total;
@@ -305,7 +311,20 @@ __device__ __forceinline__ void account_update(const AccountJob& j, int e) {
     const int cnt = end - beg;
     if (cnt <= 0) return;
     double sp = 0.0, sn = 0.0;
-    for (int r0 = beg + threadIdx.x; r0 < end; r0 += kRows * NT) {
+    if (stats) {
+        for (int r0 = beg + threadIdx.x; r0 < end; r0 += kRows * NT) {
+            float2 v[kRows];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) v[u] = stats[min(r0 + u * NT, end - 1)];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                if (r0 + u * NT >= end) break;
+                sp += static_cast<double>(v[u].y);
+                sn += static_cast<double>(sqrtf(v[u].x));
+            }
+        }
+    }
+    for (int r0 = stats ? end : beg + threadIdx.x; r0 < end; r0 += kRows * NT) {
         int tok[kRows];
         float pr[kRows], ss[kRows];
 #pragma unroll
@@ -313,7 +332,7 @@ __device__ __forceinline__ void account_update(const AccountJob& j, int e) {
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
             pr[u] = prob[static_cast<size_t>(tok[u]) * E + e];
-            const float* rp = nrm2 + static_cast<size_t>(min(r0 + u * NT, end - 1)) * stride;
+            const float* rp = nrm2 + static_cast<size_t>(min(r0 + u * NT, end - 1)) * parts;
             ss[u] = rp[0];
             for (int c = 1; c < parts; ++c) ss[u] += rp[c];
         }
@@ -434,19 +453,20 @@ int combine_chunks(const eat_params_t& p) { return (p.d_model / 4 + kThreads - 1
 hipError_t launch_combine(const eat_params_t& p, int32_t T, const uint64_t* mask, const float* gate,
                           const int32_t* inv, const void* yp, const float* ys, const uint16_t* residual,
                           void* y, float* nrm2, int splits, int64_t split_stride, const int32_t* splits_dev,
-                          bool rows_bf16, hipStream_t s) {
+                          bool rows_bf16, const float* prob, float2* stats, hipStream_t s) {
     if (splits < 1 || splits > kMaxSplits) return hipErrorInvalidValue;
     if (rows_bf16 && (splits != 1 || splits_dev || p.act_dtype != EAT_BF16)) return hipErrorInvalidValue;
     const int nchunk = combine_chunks(p);
     CombineArgs a{};
     a.mask = mask; a.gate = gate; a.inv = inv; a.yp = yp; a.splits_dev = splits_dev; a.ys = ys; a.res = residual;
+    a.prob = prob; a.stats = stats;
     a.y = y; a.nrm2 = nrm2; a.split_stride = split_stride; a.splits = splits; a.T = T; a.E = p.E; a.d = p.d_model;
     a.nchunk = nchunk; a.words = mask_words(p.E);
     if (rows_bf16) {
         a.nchunk = p.d_model / 32;
-        if (p.mode != EAT_MODE_EAT) a.nrm2 = nullptr;
         const int n8 = (p.d_model / kRowVec + kThreads - 1) / kThreads;
-        combine_rows16_kernel<<<dim3(T, n8), kThreads, 0, s>>>(a);
+        if (p.mode == EAT_MODE_EAT && stats) combine_rows16_kernel<true><<<dim3(T, n8), kThreads, 0, s>>>(a);
+        else combine_rows16_kernel<false><<<dim3(T, n8), kThreads, 0, s>>>(a);
         return hipGetLastError();
     }
     const dim3 grid(T, nchunk);

@@ -130,13 +130,14 @@ hipError_t launch_shared_bf16(const eat_params_t& p, int32_t T, const uint16_t* 
 // apart (*splits_dev of them when set, else `splits`); they are added in
 // slice order, and each row slice's sum of squares goes to nrm2.  With
 // rows_bf16 yp holds bf16 rows instead (one slice) whose sums of squares
-// are already in nrm2.  `residual` (bf16 [T][d], or null) is added to y
+// are already in nrm2, and in EAT mode the rows' (sum of squares, prob) pairs go
+// to stats [rows].  `residual` (bf16 [T][d], or null) is added to y
 // before the cast.
 hipError_t launch_combine(const eat_params_t& p, int32_t T, const uint64_t* mask,
                           const float* gate, const int32_t* inv, const void* yp,
                           const float* ys, const uint16_t* residual, void* y, float* nrm2,
                           int splits, int64_t split_stride, const int32_t* splits_dev, bool rows_bf16,
-                          hipStream_t s);
+                          const float* prob, float2* stats, hipStream_t s);
 
 // Between stacked layers (combine.hip): h = bf16(sum of `splits` fp32
 // partial rows, or the bf16 rows of src when splits == 0), written to h_out
@@ -248,7 +249,8 @@ struct AccountJob {
     const int32_t* tok_idx;
     const float* prob;
     const float* nrm2;
-    int parts, stride;       // partial sums of squares to add per row, and floats between rows in nrm2
+    const float2* stats;     // (sum of squares, probability) of each row, or null: from nrm2 and prob
+    int parts;               // partial sums of squares per row in nrm2
     int experts;
     float alpha;
     eat_accounts_t acc;
