@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(CombineArgs a) {
 // side by side in row order: the update's one workgroup per expert then reads
 // 8 contiguous bytes a row.  8192 tokens that share 4 experts: 144 us when it
 // read all 64 partials and gathered the probabilities itself, 33 when it read one
-// partial a row (a 128-byte line each, as is every gathered probability), 7 now.
+// partial a row (a 128-byte line each, as is every gathered probability), 6 now.
 constexpr int kRowVec = 8;
 template <bool STATS>
 __global__ __launch_bounds__(kThreads) void combine_rows16_kernel(CombineArgs a) {

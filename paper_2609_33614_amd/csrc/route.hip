@@ -238,75 +238,48 @@ __device__ __forceinline__ float wave_sum_j(const float (&v)[J]) {
     return wave_sum(s);
 }
 
+// History score S_h of every expert from the account snapshot (Eq. 1), by one
+// wave, into sh (64 J floats of LDS).
 template <int J>
-__global__ __launch_bounds__(256) void select_kernel(RouteArgs a) {
-    __shared__ float sh[64 * J];
-    __shared__ __align__(16) uint64_t kb[kSelWaves][64 * J];   // per-wave rank keys
-    __shared__ __align__(16) float srt[kSelWaves][64 * J];     // per-wave values in rank order
+__device__ __forceinline__ void history_scores(const RouteArgs& a, const bool (&valid)[J], float* sh) {
     const int lane = lane_id();
-    const int wave = threadIdx.x / kWave;
-    const int E = a.E;
-    bool valid[J];
-#pragma unroll
-    for (int j = 0; j < J; ++j) valid[j] = 64 * j + lane < E;
-
-    // ---- this token's partial router scores: every slice's load issued
-    // before the history score below, summed (in slice order) after it ----
-    // The kernel's loads are all issued here, before any of them is waited
-    // for, from clamped in-bounds addresses (token 0, expert 0, slice 0, or the
-    // partial-score buffer standing in for an absent trend or scale); values
-    // read for lanes past E or slices past the call's are never used.  (A load
-    // under a per-lane branch makes the compiler wait for it inside the
-    // branch, a round trip each.)
-    const int t = blockIdx.x * kSelWaves + wave;
-    const bool tok = t < a.T;
-    const int tc = tok ? t : 0;
-    float zp[J][kMaxRouteSlices];
+    double n[J], pt[J], c[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-        const float* src = a.part + static_cast<size_t>(tc) * E + (valid[j] ? 64 * j + lane : 0);
-        const size_t stride = static_cast<size_t>(a.T) * E;
-#pragma unroll
-        for (int sl = 0; sl < kMaxRouteSlices; ++sl) zp[j][sl] = src[(sl < a.slices ? sl : 0) * stride];
+        // relaxed loads: plain loads that the compiler does not move
+        // under the lane test below (and then wait for one by one)
+        const int e = valid[j] ? 64 * j + lane : 0;
+        const int64_t nv = __hip_atomic_load(a.acc_n + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const float pv = __hip_atomic_load(a.acc_p + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const float cv = __hip_atomic_load(a.acc_c + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        n[j] = valid[j] ? static_cast<double>(nv) : 0.0;
+        pt[j] = valid[j] ? static_cast<double>(pv) : 0.0;
+        c[j] = valid[j] ? static_cast<double>(cv) : 0.0;
     }
-    const int8_t trend_t = *(a.trend ? a.trend + tc : reinterpret_cast<const int8_t*>(a.part));
-    float scale[J];
+    double ln = n[0], lc = c[0];
 #pragma unroll
-    for (int j = 0; j < J; ++j) scale[j] = (a.scale ? a.scale : a.part)[valid[j] ? 64 * j + lane : 0];
-
-    // ---- history score from the account snapshot (Eq. 1) --------------
-    if (a.mode == EAT_MODE_EAT && wave == 0) {
-        double n[J], pt[J], c[J];
+    for (int j = 1; j < J; ++j) { ln += n[j]; lc += c[j]; }
+    const double sum_n = wave_sum(ln);
+    const double sum_c = a.cs_mode == 1 ? wave_sum(lc) : 0.0;
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            // relaxed loads: plain loads that the compiler does not move
-            // under the lane test below (and then wait for one by one)
-            const int e = valid[j] ? 64 * j + lane : 0;
-            const int64_t nv = __hip_atomic_load(a.acc_n + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            const float pv = __hip_atomic_load(a.acc_p + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            const float cv = __hip_atomic_load(a.acc_c + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            n[j] = valid[j] ? static_cast<double>(nv) : 0.0;
-            pt[j] = valid[j] ? static_cast<double>(pv) : 0.0;
-            c[j] = valid[j] ? static_cast<double>(cv) : 0.0;
-        }
-        double ln = n[0], lc = c[0];
-#pragma unroll
-        for (int j = 1; j < J; ++j) { ln += n[j]; lc += c[j]; }
-        const double sum_n = wave_sum(ln);
-        const double sum_c = a.cs_mode == 1 ? wave_sum(lc) : 0.0;
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const double t1 = sum_n > 0.0 ? n[j] / sum_n : 0.0;
-            const double t2 = n[j] > 0.0 ? pt[j] / n[j] : 0.0;
-            double t3 = c[j];
-            if (a.cs_mode == 1) t3 = sum_c > 0.0 ? c[j] / sum_c : 0.0;
-            sh[64 * j + lane] = static_cast<float>(a.w1 * t1 + a.w2 * t2 + a.w3 * t3);
-        }
+    for (int j = 0; j < J; ++j) {
+        const double t1 = sum_n > 0.0 ? n[j] / sum_n : 0.0;
+        const double t2 = n[j] > 0.0 ? pt[j] / n[j] : 0.0;
+        double t3 = c[j];
+        if (a.cs_mode == 1) t3 = sum_c > 0.0 ? c[j] / sum_c : 0.0;
+        sh[64 * j + lane] = static_cast<float>(a.w1 * t1 + a.w2 * t2 + a.w3 * t3);
     }
-    __syncthreads();
+}
 
-    // ---- per-token softmax, selection, renormalisation ----------------
-    if (!tok) return;
+// Everything after the scores for token t by one wave: softmax (Sec. 3.1), the
+// mode's selection and the renormalisation of Eq. 7-8.  zp: the partial scores
+// of the lane's experts; kbw, srtw: the wave's LDS scratch (64 J entries each).
+template <int J>
+__device__ __forceinline__ void select_token(const RouteArgs& a, int t, const float (&zp)[J][kMaxRouteSlices],
+                                             int8_t trend_t, const float (&scale)[J], const bool (&valid)[J],
+                                             const float* sh, uint64_t* const kbw, float* const srtw) {
+    const int lane = lane_id();
+    const int E = a.E;
     float z[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
@@ -347,8 +320,6 @@ __global__ __launch_bounds__(256) void select_kernel(RouteArgs a) {
 #pragma unroll
     for (int j = 0; j < J; ++j) nan_lanes |= ballot(valid[j] && p[j] != p[j]);
     const bool by_keys = nan_lanes == 0;
-    uint64_t* const kbw = kb[wave];
-    float* const srtw = srt[wave];
 
     uint64_t msk[J];
 #pragma unroll
@@ -526,6 +497,116 @@ __global__ __launch_bounds__(256) void select_kernel(RouteArgs a) {
     }
 }
 
+template <int J>
+__global__ __launch_bounds__(256) void select_kernel(RouteArgs a) {
+    __shared__ float sh[64 * J];
+    __shared__ __align__(16) uint64_t kb[kSelWaves][64 * J];   // per-wave rank keys
+    __shared__ __align__(16) float srt[kSelWaves][64 * J];     // per-wave values in rank order
+    const int lane = lane_id();
+    const int wave = threadIdx.x / kWave;
+    const int E = a.E;
+    bool valid[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) valid[j] = 64 * j + lane < E;
+
+    // ---- this token's partial router scores: every slice's load issued
+    // before the history score below, summed (in slice order) after it ----
+    // The kernel's loads are all issued here, before any of them is waited
+    // for, from clamped in-bounds addresses (token 0, expert 0, slice 0, or the
+    // partial-score buffer standing in for an absent trend or scale); values
+    // read for lanes past E or slices past the call's are never used.  (A load
+    // under a per-lane branch makes the compiler wait for it inside the
+    // branch, a round trip each.)
+    const int t = blockIdx.x * kSelWaves + wave;
+    const bool tok = t < a.T;
+    const int tc = tok ? t : 0;
+    float zp[J][kMaxRouteSlices];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const float* src = a.part + static_cast<size_t>(tc) * E + (valid[j] ? 64 * j + lane : 0);
+        const size_t stride = static_cast<size_t>(a.T) * E;
+#pragma unroll
+        for (int sl = 0; sl < kMaxRouteSlices; ++sl) zp[j][sl] = src[(sl < a.slices ? sl : 0) * stride];
+    }
+    const int8_t trend_t = *(a.trend ? a.trend + tc : reinterpret_cast<const int8_t*>(a.part));
+    float scale[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) scale[j] = (a.scale ? a.scale : a.part)[valid[j] ? 64 * j + lane : 0];
+
+    if (a.mode == EAT_MODE_EAT && wave == 0) history_scores<J>(a, valid, sh);
+    __syncthreads();
+    if (!tok) return;
+    select_token<J>(a, t, zp, trend_t, scale, valid, sh, kb[wave], srt[wave]);
+}
+
+// Scores and selection of calls of fewer than 1024 tokens in one launch, for
+// routers of up to 16 experts and 16 KB: a workgroup of 16 waves per 16 tokens,
+// wave w taking d slice w of the scores (the logits kernel's four interleaved
+// k-step chains in four accumulators, added in its order: the same bits), then
+// token w's selection.  A workgroup reads the whole router matrix: within what a
+// CU keeps in flight (about 32 KB) that costs less than the ~4 us of the launch it
+// saves (8 experts x 128, 32 tokens, whole fp32 layer 28.4 -> 25.3 us); at 8 x
+// 4096 it takes 19.7 us against 9.4 for the two launches.
+constexpr int kSmallRouterBytes = 16 << 10;
+constexpr int kSmallExperts = 16;
+template <typename XT>
+__global__ __launch_bounds__(16 * kWave) void route_small_kernel(RouteArgs a) {
+    __shared__ float part[kMaxRouteSlices][16][kSmallExperts];
+    __shared__ float sh[64];
+    __shared__ __align__(16) uint64_t kb[16][64];
+    __shared__ __align__(16) float srt[16][64];
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    const int t0 = blockIdx.x * 16, E = a.E;
+    const bool valid[1] = {lane < E};
+    const int t = t0 + wave, tc = t < a.T ? t : 0;
+    const int8_t trend_t = *(a.trend ? a.trend + tc : reinterpret_cast<const int8_t*>(a.w_router));
+    const float scale[1] = {(a.scale ? a.scale : a.w_router)[valid[0] ? lane : 0]};
+    if (wave < a.slices) {
+        const int kq = 4 * (lane >> 4), i16 = lane & 15;
+        const int per = a.d / 16 / a.slices, sbeg = wave * per, send = sbeg + per;
+        // (token rows past T and experts past E read row 0; their scores are not used)
+        const XT* xrow = static_cast<const XT*>(a.x) + static_cast<size_t>(t0 + i16 < a.T ? t0 + i16 : 0) * a.d + kq;
+        const float* wrow = a.w_router + static_cast<size_t>(i16 < E ? i16 : 0) * a.d + kq;
+        f32x4 acc[kLogitWaves];
+#pragma unroll
+        for (int v = 0; v < kLogitWaves; ++v) acc[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int st = sbeg; st < send; st += 2 * kLogitWaves) {
+            float xv[2 * kLogitWaves][4];
+            float4 wv[2 * kLogitWaves];
+#pragma unroll
+            for (int u = 0; u < 2 * kLogitWaves; ++u) {
+                const int k = 16 * min(st + u, send - 1);
+                load_x4<XT>(xrow, k, xv[u]);
+                wv[u] = *reinterpret_cast<const float4*>(wrow + k);
+            }
+#pragma unroll
+            for (int u = 0; u < 2 * kLogitWaves; ++u) {
+                if (st + u >= send) break;    // uniform
+                f32x4& c = acc[u % kLogitWaves];
+                c = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[u][0], wv[u].x, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[u][1], wv[u].y, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[u][2], wv[u].z, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[u][3], wv[u].w, c, 0, 0, 0);
+            }
+        }
+        // lane holds tokens kq + i, expert lane % 16
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float sum = 0.f;
+#pragma unroll
+            for (int v = 0; v < kLogitWaves; ++v) sum += acc[v][i];
+            part[wave][kq + i][i16] = sum;
+        }
+    }
+    if (a.mode == EAT_MODE_EAT && wave == 15) history_scores<1>(a, valid, sh);
+    __syncthreads();
+    if (t >= a.T) return;
+    float zp[1][kMaxRouteSlices];
+#pragma unroll
+    for (int sl = 0; sl < kMaxRouteSlices; ++sl) zp[0][sl] = part[sl < a.slices ? sl : 0][wave][valid[0] ? lane : 0];
+    select_token<1>(a, t, zp, trend_t, scale, valid, sh, kb[wave], srt[wave]);
+}
+
 template <typename XT, int NT>
 hipError_t launch_logits_n(const RouteArgs& a, int tt, dim3 grid, hipStream_t s) {
     if (tt == 4) logits_kernel<XT, NT, 4><<<grid, 256, 0, s>>>(a);
@@ -536,6 +617,10 @@ hipError_t launch_logits_n(const RouteArgs& a, int tt, dim3 grid, hipStream_t s)
 template <typename XT>
 hipError_t launch_route_t(const RouteArgs& a, hipStream_t s) {
     const int tt = route_token_tiles(a.T);
+    if (a.E <= kSmallExperts && a.E * a.d * 4 <= kSmallRouterBytes && tt == 1) {
+        route_small_kernel<XT><<<(a.T + 15) / 16, 16 * kWave, 0, s>>>(a);
+        return hipGetLastError();
+    }
     const int words = mask_words(a.E);
     const dim3 grid((a.T + 16 * tt - 1) / (16 * tt), a.slices, words);
     hipError_t err;
