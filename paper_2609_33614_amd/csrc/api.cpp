@@ -510,7 +510,8 @@ eat_status_t eat_ppl_trend(const void* h, int32_t S, int32_t d, const void* w_vo
     hipError_t e = eat::launch_head_bf16(static_cast<const uint16_t*>(h), S, static_cast<const uint16_t*>(w_vocab),
                                          V, d, z, splits, stride, stream);
     if (e == hipSuccess)
-        e = eat::launch_ppl(z, splits, stride, S, V, target, nll_sum, count, ppl_prev, trend_out, nll_out, stream);
+        e = eat::launch_ppl(z, splits, stride, S, V, static_cast<const uint16_t*>(h),
+                            static_cast<const uint16_t*>(w_vocab), d, target, nll_sum, count, ppl_prev, trend_out, nll_out, stream);
     return e == hipSuccess ? EAT_OK : EAT_ERR_HIP;
 }
 

@@ -228,7 +228,8 @@ hipError_t launch_pack(const uint16_t* src, int32_t groups, int32_t M, int32_t K
 // running per-sequence state (fp64 NLL sum, count, previous perplexity) and
 // the int8 trend; z holds `splits` slices `stride` floats apart.
 // launch_ppl_reset zeroes the state.
-hipError_t launch_ppl(const float* z, int splits, int64_t stride, int32_t S, int V, const int32_t* target,
+hipError_t launch_ppl(const float* z, int splits, int64_t stride, int32_t S, int V, const uint16_t* h,
+                      const uint16_t* w_vocab, int d, const int32_t* target,
                       double* nll_sum, int32_t* count, double* ppl_prev, int8_t* trend, float* nll_out,
                       hipStream_t s);
 hipError_t launch_ppl_reset(int32_t S, double* nll_sum, int32_t* count, double* ppl_prev, hipStream_t s);

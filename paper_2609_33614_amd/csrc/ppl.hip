@@ -35,13 +35,6 @@ __device__ __forceinline__ Lse lse_merge(Lse a, Lse b) {
     return {a.m, a.s + b.s * expf(b.m - a.m)};
 }
 
-// logit j of a row: the GEMM's reduction slices added in slice order
-__device__ __forceinline__ float logit(const float* row, int splits, int64_t stride, int j) {
-    float v = row[j];
-    for (int sp = 1; sp < splits; ++sp) v += row[sp * stride + j];
-    return v;
-}
-
 // exp(v - m) of a value of a block with maximum m (the maximum itself counts
 // 1 also where it is infinite)
 __device__ __forceinline__ float term(float v, float m) { return v == m ? 1.f : expf(v - m); }
@@ -50,13 +43,35 @@ __device__ __forceinline__ float term(float v, float m) { return v == m ? 1.f : 
 // a CU, less than the launch that a split over more workgroups needs to merge
 // its parts (16 chunks a row, 256 threads each, and a finishing launch: 14.4 us
 // at 64 x 32000 against 6.5).
+// The target's logit, on whose rounding the NLL would depend most, is taken
+// again from the hidden row and the head's row in fp64 (16 KB, under the logits'
+// latency).
 __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__ z, int splits, int64_t stride, int V,
+                                                       const uint16_t* __restrict__ h,
+                                                       const uint16_t* __restrict__ w_vocab, int d,
                                                        const int32_t* __restrict__ target, double* nll_sum,
                                                        int32_t* count, double* ppl_prev, int8_t* trend,
                                                        float* nll_out) {
     __shared__ Lse red[kWaves];
+    __shared__ double zred[kWaves];
     const int s = blockIdx.x;
     const float* row = z + static_cast<size_t>(s) * V;
+    const int y = target[s];
+    const bool known = y >= 0 && y < V;
+    double zt = 0.0;
+    for (int k = 4 * threadIdx.x; k < d; k += 4 * kThreads) {     // (d is a multiple of 64)
+        const uint2 p = *reinterpret_cast<const uint2*>(h + static_cast<size_t>(s) * d + k);
+        const uint2 q = *reinterpret_cast<const uint2*>(w_vocab + static_cast<size_t>(known ? y : 0) * d + k);
+        const uint32_t pw[2] = {p.x, p.y}, qw[2] = {q.x, q.y};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            // (a product of two bf16 values is exact in fp32)
+            zt += static_cast<double>(__uint_as_float(pw[i] << 16) * __uint_as_float(qw[i] << 16));
+            zt += static_cast<double>(__uint_as_float(pw[i] & 0xffff0000u) * __uint_as_float(qw[i] & 0xffff0000u));
+        }
+    }
+    zt = wave_sum(zt);
+    if (lane_id() == 0) zred[threadIdx.x / kWave] = zt;
     Lse a{-INFINITY, 0.f};
     // (V is a multiple of 64)
     for (int j0 = 4 * threadIdx.x; j0 < V; j0 += 4 * kThreads * kVec) {
@@ -95,11 +110,10 @@ __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__
     Lse t = red[0];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) t = lse_merge(t, red[w]);
-    const int y = target[s];
-    double nll = NAN;
-    if (y >= 0 && y < V)
-        nll = static_cast<double>(t.m) + log(static_cast<double>(t.s)) -
-              static_cast<double>(logit(row, splits, stride, y));
+    zt = zred[0];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) zt += zred[w];
+    const double nll = known ? static_cast<double>(t.m) + log(static_cast<double>(t.s)) - zt : NAN;
     const double sum = nll_sum[s] + nll;
     const int32_t n = count[s] + 1;
     const double ppl = exp(sum / n);
@@ -118,10 +132,11 @@ __global__ __launch_bounds__(kThreads) void ppl_reset_kernel(int S, double* nll_
 
 }  // namespace
 
-hipError_t launch_ppl(const float* z, int splits, int64_t stride, int32_t S, int V, const int32_t* target,
+hipError_t launch_ppl(const float* z, int splits, int64_t stride, int32_t S, int V, const uint16_t* h,
+                      const uint16_t* w_vocab, int d, const int32_t* target,
                       double* nll_sum, int32_t* count, double* ppl_prev, int8_t* trend, float* nll_out,
                       hipStream_t s) {
-    ppl_kernel<<<S, kThreads, 0, s>>>(z, splits, stride, V, target, nll_sum, count, ppl_prev, trend, nll_out);
+    ppl_kernel<<<S, kThreads, 0, s>>>(z, splits, stride, V, h, w_vocab, d, target, nll_sum, count, ppl_prev, trend, nll_out);
     return hipGetLastError();
 }
 
