@@ -19,8 +19,11 @@
 // work items over about as many workgroups as the chip keeps resident.
 // Weights may be in the packed layout (pack.hip), read one contiguous
 // kilobyte per load instruction with the streaming cache policy.
-// Prefill-sized calls (hundreds of rows per expert) go to the wide MFMA
-// tiles of wide.hip instead.
+// Calls of more than 64 tokens go to the MFMA tiles of wide.hip instead,
+// unless d_model or d_ffn is too short for their ring (below 192); the
+// 128-token tiles here serve those layers and the mixing projection of stacked
+// layers.  (Figures below for 128-token tiles on the named layers' calls of more
+// than 64 tokens were measured when those calls still ran here.)
 //
 // fp32 path: fp32 MFMA tiles, for layers whose weights are fp32 (small
 // correctness-sized layers).
@@ -927,10 +930,8 @@ static int expected_tiles(const eat_params_t& p, int32_t T) {
     return static_cast<int>(std::max<int64_t>(active, (assign + bn - 1) / bn));
 }
 
-// Calls averaging at least this many rows per expert take the wide MFMA
-// tiles.  Measured at 32 (the fine-grained layer's 256-token decode then
-// goes wide): Top-K +4%, EAT -2% -- EAT's ~8 experts leave the wide tiles
-// ~66 work items for 256 CUs, and its down projection slows from 31 to 42 us.
+// Calls averaging at least this many rows per expert take the 256 x 256 tiles
+// and store the expert rows in bf16; smaller ones keep fp32 rows.
 #ifndef EAT_WIDE_ROWS
 #define EAT_WIDE_ROWS 256
 #endif
