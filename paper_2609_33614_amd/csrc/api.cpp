@@ -264,7 +264,7 @@ hipError_t forward_impl(const eat_ctx& h, const void* x, int32_t T, const float*
         e = eat::launch_route(p, x, T, w_router, acc, ppl_trend, b.lpart, b.mask, b.k, b.gate, b.prob, stream);
     mark(EAT_STAGE_ROUTED);
     Segments seg{};
-    if (T <= eat::kFusedTokens)
+    if (eat::fuses_permutation(p, T))
         seg = Segments{b.mask, T, eat::mask_words(p.E), b.offsets, b.tok_idx, b.inv, expert_load_out};
     else if (e == hipSuccess)
         e = eat::launch_permute(p, T, b.mask, b.offsets, b.tok_idx, b.inv, expert_load_out, stream);

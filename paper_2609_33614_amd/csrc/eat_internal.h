@@ -66,9 +66,11 @@ struct Buffers {
 // The token -> expert permutation of a call of at most kFusedTokens tokens is
 // worked out by the up/gate launch itself, from the selection masks
 // (eat_device.h): every workgroup the part it needs, and the launch also
-// writes the arrays that launch_permute writes for larger calls.  mask null:
-// they are already there.
+// writes the arrays that launch_permute writes for other calls.  mask null:
+// they are already there.  fuses_permutation decides which it is, for the
+// caller and for the expert launchers, which refuse a mask that contradicts it.
 constexpr int kFusedTokens = 256;
+bool fuses_permutation(const eat_params_t& p, int32_t T);
 struct Segments {
     const uint64_t* mask;    // [T][words]
     int T, words;

@@ -976,6 +976,11 @@ static bool shared_mid(const eat_params_t& p, int32_t T) {
 
 bool rows_bf16(const eat_params_t& p, int32_t T) { return use_wide(p, T); }
 
+// Every expert kernel but the prefill tile works the permutation of a small
+// call out.  The two sizes meet at 256 tokens with top_k = E, whose experts
+// hold 256 rows each: a prefill-sized call, with the permutation launch.
+bool fuses_permutation(const eat_params_t& p, int32_t T) { return T <= kFusedTokens && !use_wide(p, T); }
+
 int norm_parts(const eat_params_t& p, int32_t T) {
     return rows_bf16(p, T) ? p.d_model / 32 : combine_chunks(p);
 }
@@ -1065,6 +1070,7 @@ hipError_t launch_experts_f32(const eat_params_t& p, int32_t T, int64_t rows_cap
                               const float* w1, const float* w3, const float* w2,
                               const int32_t* offsets, const int32_t* tok_idx, const Segments& seg, float* h,
                               float* yp, hipStream_t s, const std::function<void()>& between) {
+    if ((seg.mask != nullptr) != fuses_permutation(p, T)) return hipErrorInvalidValue;
     const int64_t per_expert = (T + kF32Tok - 1) / kF32Tok;
     const int64_t tiles = std::min<int64_t>({rows_cap, per_expert * p.E, (rows_cap + kF32Tok - 1) / kF32Tok + p.E});
     return launch_f32_pair(x, w1, w3, w2, tok_idx, offsets, 0, p.E, p.d_model, p.d_ffn, tiles, seg, h, yp, s, between);
@@ -1082,6 +1088,7 @@ hipError_t launch_experts_bf16(const eat_params_t& p, int32_t T, int64_t rows_ca
                                const int32_t* offsets, const int32_t* tok_idx, const Segments& seg, uint16_t* h,
                                float* gu, float* yp, float* nrm2, int32_t* up_splits_dev, int32_t* down_splits_dev,
                                hipStream_t s, const std::function<void()>& between) {
+    if ((seg.mask != nullptr) != fuses_permutation(p, T)) return hipErrorInvalidValue;
     const int nsub = pick_nsub(T);
     const int bn = 16 * nsub;
     // no expert holds more than T rows, so it needs at most ceil(T / bn) tiles

@@ -1,5 +1,6 @@
-// Token -> expert permutation (gfx950) of calls of more than kFusedTokens
-// tokens (smaller ones work it out in the up/gate launch, eat_device.h).
+// Token -> expert permutation (gfx950) of calls whose up/gate launch does not
+// work it out (fuses_permutation): those of more than kFusedTokens tokens and
+// prefill-sized ones of 256.
 //
 // The selected (token, expert) pairs are laid out expert-major: expert e
 // owns rows [offsets[e], offsets[e+1]), and inside that range its tokens

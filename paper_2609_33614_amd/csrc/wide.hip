@@ -254,7 +254,7 @@ __global__ __launch_bounds__(C::kThreads) void wide_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint8_t ring[C::STAGES * C::kStage];
     __shared__ int tstart[kMaxExperts + 1];
     __shared__ int soff[kMaxExperts + 1];     // the segment offsets, read per item without a memory wait
-    // (the prefill tile never serves calls that small)
+    // (the prefill tile's calls come with the permutation launch, whatever their size)
     constexpr bool kFuse = GATED && C::TM * C::NW < 256 * 256;
     constexpr int NC = kFusedTokens / kWave;
     __shared__ uint64_t cols[kFuse ? kMaxExperts * NC : 1];

@@ -28,3 +28,15 @@ def test_fused_permutation(case, T, mode):
     shape, w, lay, prm = P._layer(c, mode, K=min(P.SHAPES[c["shape"]].K, c["E"]), max_tokens=T)
     acc = make_accounts(c["E"], seed=T, c_scale=0.05)
     P._forward_check(f"permute {case} {mode} T={T}", lay, shape, P._x_host(shape, T, c["d"], seed=T), w, prm, acc=acc)
+
+
+@pytest.mark.parametrize("E", [1, 8])
+@pytest.mark.parametrize("T", [255, 256, 257])
+@pytest.mark.parametrize("mode", ["eat", "topk", "topp"])
+def test_top_k_of_every_expert(E, T, mode):
+    """K = E: at 256 tokens the experts' average of 256 rows makes it a
+    prefill-sized call, which takes the permutation launch."""
+    c = dict(shape="mixtral", d=512, F=768, E=E, Fs=0)
+    shape, w, lay, prm = P._layer(c, mode, K=E, max_tokens=T)
+    acc = make_accounts(E, seed=T, c_scale=0.05)
+    P._forward_check(f"permute K=E={E} {mode} T={T}", lay, shape, P._x_host(shape, T, c["d"], seed=T), w, prm, acc=acc)
