@@ -7,7 +7,7 @@
 // ppl_kernel, one workgroup per sequence, folds the row into an online
 // logsumexp pair (running max, sum of exp(z - max)): a thread's values a block
 // at a time, then the wave by butterfly, then the waves in order; its first
-// thread forms NLL = logsumexp - z[target] and the sequence's running state in
+// thread forms the NLL from it and z[target] and the sequence's running state in
 // fp64: sum of NLL, token count, perplexity exp(sum / count) and the trend (+1
 // rose since the previous token, -1 did not, 0 first token).  Every merge has a
 // fixed order, so results are bit-reproducible.
@@ -29,15 +29,15 @@ struct Lse {
     float m, s;
 };
 
+// exp(v - m) of a value with maximum m (the maximum itself counts 1 also where
+// it is infinite)
+__device__ __forceinline__ float term(float v, float m) { return v == m ? 1.f : expf(v - m); }
+
+// (a pair of nothing but -inf holds s = 0, or NaN from NaN logits, which stays)
 __device__ __forceinline__ Lse lse_merge(Lse a, Lse b) {
     if (a.m < b.m) { const Lse t = a; a = b; b = t; }
-    if (b.m == -INFINITY) return a;
-    return {a.m, a.s + b.s * expf(b.m - a.m)};
+    return {a.m, a.s + b.s * term(b.m, a.m)};
 }
-
-// exp(v - m) of a value of a block with maximum m (the maximum itself counts
-// 1 also where it is infinite)
-__device__ __forceinline__ float term(float v, float m) { return v == m ? 1.f : expf(v - m); }
 
 // One workgroup per sequence: 128 KB of logits are a latency and a few us for
 // a CU, less than the launch that a split over more workgroups needs to merge
@@ -45,7 +45,10 @@ __device__ __forceinline__ float term(float v, float m) { return v == m ? 1.f : 
 // at 64 x 32000 against 6.5).
 // The target's logit, on whose rounding the NLL would depend most, is taken
 // again from the hidden row and the head's row in fp64 (16 KB, under the logits'
-// latency).
+// latency), on both sides of the NLL: the row's logsumexp leaves the target out,
+// and NLL = log(1 + exp(rest - z[target])).  It is never negative, and its
+// error is the rest's times the probability of the rest, however confident the
+// prediction.
 __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__ z, int splits, int64_t stride, int V,
                                                        const uint16_t* __restrict__ h,
                                                        const uint16_t* __restrict__ w_vocab, int d,
@@ -65,9 +68,10 @@ __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__
         const uint32_t pw[2] = {p.x, p.y}, qw[2] = {q.x, q.y};
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            // (a product of two bf16 values is exact in fp32)
-            zt += static_cast<double>(__uint_as_float(pw[i] << 16) * __uint_as_float(qw[i] << 16));
-            zt += static_cast<double>(__uint_as_float(pw[i] & 0xffff0000u) * __uint_as_float(qw[i] & 0xffff0000u));
+            zt = fma(static_cast<double>(__uint_as_float(pw[i] << 16)),
+                     static_cast<double>(__uint_as_float(qw[i] << 16)), zt);
+            zt = fma(static_cast<double>(__uint_as_float(pw[i] & 0xffff0000u)),
+                     static_cast<double>(__uint_as_float(qw[i] & 0xffff0000u)), zt);
         }
     }
     zt = wave_sum(zt);
@@ -88,6 +92,14 @@ __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__
                 const float4 q = *reinterpret_cast<const float4*>(row + sp * stride + (j < V ? j : j0));
                 v[i].x += q.x; v[i].y += q.y; v[i].z += q.z; v[i].w += q.w;
             }
+#pragma unroll
+        for (int i = 0; i < kVec; ++i) {
+            const int at = (known ? y : -1) - (j0 + 4 * kThreads * i);     // the target counts as no logit
+            if (at == 0) v[i].x = -INFINITY;
+            if (at == 1) v[i].y = -INFINITY;
+            if (at == 2) v[i].z = -INFINITY;
+            if (at == 3) v[i].w = -INFINITY;
+        }
         Lse b{-INFINITY, 0.f};
 #pragma unroll
         for (int i = 0; i < kVec; ++i)
@@ -96,6 +108,7 @@ __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__
         for (int i = 0; i < kVec; ++i)
             if (j0 + 4 * kThreads * i < V)
                 b.s += (term(v[i].x, b.m) + term(v[i].y, b.m)) + (term(v[i].z, b.m) + term(v[i].w, b.m));
+        if (b.m == -INFINITY) b.s -= b.s;     // no logit above -inf: 0, or NaN
         a = lse_merge(a, b);
     }
 #pragma unroll
@@ -113,7 +126,11 @@ __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__
     zt = zred[0];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) zt += zred[w];
-    const double nll = known ? static_cast<double>(t.m) + log(static_cast<double>(t.s)) - zt : NAN;
+    const double rest = static_cast<double>(t.m) + log(static_cast<double>(t.s));
+    // (zt - zt is NaN for an infinite target, as its row's logsumexp less itself)
+    const double nll = !known ? NAN
+                       : zt >= rest ? log1p(exp(rest - zt)) + (zt - zt)
+                                    : rest - zt + log1p(exp(zt - rest));
     const double sum = nll_sum[s] + nll;
     const int32_t n = count[s] + 1;
     const double ppl = exp(sum / n);

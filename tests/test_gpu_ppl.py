@@ -120,3 +120,83 @@ def test_ppl_trend_drives_the_next_step():
     assert cmp.mean() > 0.8
     PT.report("ppl -> routing", compared=int(cmp.sum()), rising=int((trend_o > 0).sum()))
     lay.close()
+
+
+def _step(h, head, target):
+    sig = PplSignal(h.shape[0], head.cuda())
+    sig.reset()
+    sig.step(h.cuda(), torch.as_tensor(target, dtype=torch.int32).cuda())
+    torch.cuda.synchronize()
+    return sig.nll.cpu().double()
+
+
+@pytest.mark.parametrize("S,d,V", [(40, 4096, 1024), (64, 512, 8192), (9, 128, 4160), (400, 256, 512)])
+def test_confident_targets(S, d, V):
+    """Targets whose logit stands 0 to 45 above the others, as a trained model's
+    do.  NLL = log(1 + R), R = exp(rest - z_y): a logit of the rest that is off
+    by eps moves it by eps (1 - p_y) (1 - p_y = R / (1 + R)).  eps: an fp32 sum
+    of d products of bf16 values is off by at most d 2^-24 sum |h w|; the fp32
+    sum of V exponentials (64 additions deep at most) and their arguments add
+    some 2^-24 of themselves each; the result is rounded to fp32 once."""
+    g = torch.Generator().manual_seed(S + d + V)
+    h = torch.randn(S, d, generator=g).to(torch.bfloat16)
+    head = (torch.randn(V, d, generator=g) * d ** -0.5).to(torch.bfloat16)
+    target = torch.randperm(V, generator=g)[:S]
+    lift = torch.linspace(0.0, 45.0, S)
+    head[target] = (head[target].float() + lift[:, None] * h.float() / h.float().square().sum(1, keepdim=True)).to(
+        torch.bfloat16)
+    nll = _step(h, head, target)
+    z = h.double() @ head.double().T
+    zy = z.gather(1, target[:, None])[:, 0]
+    rest = torch.logsumexp(z.scatter(1, target[:, None], -np.inf), 1)
+    ref = torch.nn.functional.softplus(rest - zy, threshold=1e9)
+    eps = (d * 2.0 ** -24 * (h.double().abs() @ head.double().abs().T).max(1).values
+           + 2.0 ** -24 * (80 + 4 * z.abs().max(1).values))
+    bound = -torch.expm1(-ref) * eps * (1 + eps) + 2.0 ** -24 * ref
+    err = (nll - ref).abs()
+    PT.report(f"ppl confident S={S} d={d} V={V}", least_nll=f"{ref.min():.1e}",
+              max_err_over_nll=f"{(err / ref).max():.1e}", max_err_over_bound=f"{(err / bound).max():.1e}")
+    assert (nll >= 0).all()
+    assert (err <= bound).all()
+
+
+@pytest.mark.parametrize("V,d", [(64, 128), (4160, 192), (33024, 256)])
+def test_nonfinite_logits(V, d):
+    """Infinities and NaN in hidden rows and in head rows: what logsumexp(z) - z_y
+    gives for the target and for the rest, in every column a thread may hold
+    alone; the other sequences keep their value bit for bit."""
+    S = 8
+    g = torch.Generator().manual_seed(V)
+    h = torch.randn(S, d, generator=g).to(torch.bfloat16)
+    head = (torch.randn(V, d, generator=g) * d ** -0.5).to(torch.bfloat16)
+    target = torch.randint(0, V - 8, (S,), generator=g)
+    clean = _step(h, head, target)
+    assert torch.isfinite(clean).all()
+    bad = h.clone()
+    bad[1] = np.nan
+    bad[4, 3] = np.inf                           # logits of both signs
+    got = _step(bad, head, target)
+    keep = [s for s in range(S) if s not in (1, 4)]
+    assert torch.equal(got[keep], clean[keep]) and torch.isnan(got[1])
+    assert not torch.isfinite(got[4])
+    # head rows: h[:, 0] = 1 picks +-inf logits, the same for every sequence
+    h2 = h.clone()
+    h2[:, 0] = 1.0
+    for cols, value, expect in [((V - 1,), np.nan, np.nan), (tuple(range(V - 4, V)), np.nan, np.nan),
+                                ((V - 2,), np.inf, np.inf), ((V - 1, V - 7), np.inf, np.inf),
+                                (tuple(range(V - 4, V)), -np.inf, None)]:
+        w = head.clone()
+        w[list(cols), 0] = value
+        n = _step(h2, w, target)
+        if expect is None:                       # -inf: exp gives 0, as the columns' absence
+            z = h2.double() @ w.double().T
+            ref = torch.logsumexp(z, 1) - z.gather(1, target[:, None])[:, 0]
+            torch.testing.assert_close(n, ref, rtol=1e-4, atol=1e-5)
+        else:
+            assert torch.isnan(n).all() if np.isnan(expect) else (n == expect).all(), (cols, value, n)
+    # the target itself
+    for value, check in [(np.inf, torch.isnan), (np.nan, torch.isnan), (-np.inf, torch.isposinf)]:
+        w = head.clone()
+        w[target[0], 0] = value
+        n = _step(h2, w, target)
+        assert check(n[0]), (value, n[0])
