@@ -7,8 +7,7 @@
 // fragment of lane l = 16 q + i holds W[g][16 rb + i][32 ks + 8 q .. + 7].
 // A wave that owns 16 weight rows then reads each k-step of them as one
 // contiguous kilobyte, which the decode kernels load with the streaming
-// cache policy; the prefill tiles gather the same fragments into their LDS
-// rows.  Packing is a permutation: results are bit-identical to the
+// cache policy, and the MFMA tiles copy to LDS block by block.  Packing is a permutation: results are bit-identical to the
 // row-major layout.
 #include "eat_device.h"
 #include "eat_internal.h"

@@ -102,6 +102,18 @@ constexpr int kRowsPerLine = 256 / kRB;
 __device__ __forceinline__ int swz(int r) { return (static_cast<unsigned>(r) / kRowsPerLine) & (kVPR - 1); }
 __device__ __forceinline__ int wswz(int r, int v) { return r * kRB + ((v ^ swz(r)) << 4); }
 
+// The same for weight rows, which packed weights keep in LDS in their own
+// order (pack.hip): a 1 KB block per 16 rows and 32 reduction elements, a
+// fragment of 16 consecutive rows one line.  A load instruction then copies one
+// contiguous kilobyte; gathered into 128-byte rows, every lane of a quad
+// fetched from another line, and packed weights were slower than row-major
+// ones (8 experts, 1024 EAT tokens on Wide tiles 893 against 832 us, now 836; 256
+// Top-K tokens on Mid tiles 551 against 521, now 524).
+template <bool PACKED>
+__device__ __forceinline__ int weight_at(int r, int v) {
+    return PACKED ? (((r >> 4) * 2 + (v >> 2)) << 10) + (((v & 3) * 16 + (r & 15)) << 4) : wswz(r, v);
+}
+
 // One work item: token rows [r0, r0 + n) of expert e's segment against the
 // expert's weight rows from m0 (W1 and W3 rows m0.. in the gated tile), over
 // reduction slice sp.
@@ -111,9 +123,9 @@ struct Item {
 
 // Lane l of a DMA instruction writes LDS bytes [16 l, 16 l + 16) of its 1 KB
 // block = row l / kVPR, slot l % kVPR; it fetches the global vector that
-// belongs in that slot under the swizzle.  Blocks j < kBT hold token rows (a
-// 64-bit source per lane: rows are gathered), the others weight rows of
-// expert e -- one matrix per block (W1 or W3 in the gated tile), so the
+// belongs in that slot under the swizzle (packed weights, weight block b: vector
+// l of 16-row group b / 2 and k-step b % 2).  Token blocks have a 64-bit source per
+// lane (rows are gathered), weight blocks hold rows of expert e -- one matrix per block (W1 or W3 in the gated tile), so the
 // block's base is uniform and each lane keeps a 32-bit element offset into
 // the expert's matrix (M K < 2^31, checked on the host).
 template <class C>
@@ -154,17 +166,18 @@ __device__ __forceinline__ ItemLoads<C> item_loads(const WideArgs& a, const Item
     }
 #pragma unroll
     for (int j = 0; j < C::kBW; ++j) {
-        const int rb0 = kRPB * (wave + C::kWaves * j);        // the block's first weight row
-        const int r = rb0 + lane / kVPR;
-        const int v = slot ^ swz(r);
+        const int b = wave + C::kWaves * j;
+        const int rb0 = PACKED ? 16 * (b / 2) : kRPB * b;     // the block's first weight row
         // (a last tile past M, where M is not a multiple of NW, loads rows of
         // the matrix again; their results are not stored)
-        const int row = min(it.m0 + (GATED ? (r & (C::NW / 2 - 1)) : r), a.M - 1);
-        // packed: vector v of a chunk is k-step v / 4 of the chunk,
-        // fragment (v % 4, row % 16) of that step's block (pack.hip)
-        L.woff[j] = PACKED ? static_cast<uint32_t>(((row / 16) * (a.K / 32) + kbeg / 32 + (v >> 2)) * 512 +
-                                                   8 * (16 * (v & 3) + (row & 15)))
-                           : static_cast<uint32_t>(row * a.K + kbeg + 8 * v);
+        if constexpr (PACKED) {
+            const int row = min(it.m0 + (GATED ? (rb0 & (C::NW / 2 - 1)) : rb0), a.M - 16);
+            L.woff[j] = static_cast<uint32_t>(((row / 16) * (a.K / 32) + kbeg / 32 + (b & 1)) * 512 + 8 * lane);
+        } else {
+            const int r = rb0 + lane / kVPR;
+            const int row = min(it.m0 + (GATED ? (r & (C::NW / 2 - 1)) : r), a.M - 1);
+            L.woff[j] = static_cast<uint32_t>(row * a.K + kbeg + 8 * (slot ^ swz(r)));
+        }
         L.wbase[j] = (GATED && rb0 >= C::NW / 2 ? a.wb : a.wa) + emat;
     }
     return L;
@@ -420,7 +433,7 @@ __global__ __launch_bounds__(C::kThreads) void wide_kernel(WideArgs a) {
                     B[j] = *reinterpret_cast<const bf16x8*>(st + wswz(brow + 32 * j + l32, v));
 #pragma unroll
                 for (int i = 0; i < WF; ++i)
-                    A[i] = *reinterpret_cast<const bf16x8*>(st + C::kRegion + wswz(arow(i) + l32, v));
+                    A[i] = *reinterpret_cast<const bf16x8*>(st + C::kRegion + weight_at<PACKED>(arow(i) + l32, v));
 #pragma unroll
                 for (int j = 0; j < TF; ++j)
 #pragma unroll
