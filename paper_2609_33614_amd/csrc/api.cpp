@@ -78,8 +78,9 @@ Workspace plan_workspace(const eat_ctx& c, int32_t T) {
     w.tok_idx = take(rows * 4);
     w.inv = take(t * E * 4);
     w.h = take(rows * p.d_ffn * es);
-    w.gu = take(w.up_splits > 1 ? 2 * static_cast<size_t>(w.up_splits) * rows * p.d_ffn * 4 : 0);
-    w.yp = take(static_cast<size_t>(w.splits) * rows * p.d_model * 4);
+    // (the gate/up partials are added up before the down projection writes its slices)
+    const size_t gu = w.up_splits > 1 ? 2 * static_cast<size_t>(w.up_splits) * rows * p.d_ffn * 4 : 0;
+    w.gu = w.yp = take(std::max(gu, static_cast<size_t>(w.splits) * rows * p.d_model * 4));
     w.nrm = take(rows * static_cast<size_t>(norm_parts(p, T)) * 4);
     w.shared_splits = p.d_shared ? shared_splits(p, T) : 1;
     w.shared_up_splits = p.d_shared ? shared_up_splits(p, T) : 1;

@@ -201,11 +201,15 @@ bool mid_fits(int M, int K);
 // again (about 5 TB/s).  A slice keeps four chunks.  One item too many costs a
 // whole round: the Mixtral-shaped down projection of 500 tokens took 220 us
 // with 8 token tiles (256 items) and 430 with 9 (288).
+// (kRoundItems: the part's CUs, each with one tile workgroup.  It and the times
+// only steer the choice, on host and device alike; on a part with another count
+// results are the same and the choice less good.)
+constexpr int kRoundItems = 256;
 __host__ __device__ inline int tile_split(int64_t items, int K, int max_splits, int64_t rows, int M, int chunk_ns) {
     int best = 1;
     int64_t least = 0;
     for (int s = 1; s <= max_splits && (K / 64) % s == 0 && K / 64 / s >= 4; s *= 2) {
-        const int64_t cost = (items * s + 255) / 256 * (K / 64 / s) * chunk_ns + s * rows * M / 625;
+        const int64_t cost = (items * s + kRoundItems - 1) / kRoundItems * (K / 64 / s) * chunk_ns + s * rows * M / 625;
         if (s == 1 || cost < least) {
             best = s;
             least = cost;

@@ -948,19 +948,70 @@ static bool use_wide(const eat_params_t& p, int32_t T) {
 // 128 experts, 1000 tokens, 375 -> 311; 60 experts, 128 tokens, 315 -> 250;
 // 8 of 64 experts, 256 tokens, 89 -> 74.  Up to 64 tokens the streaming
 // kernel reads packed weights at 5.8-6.1 TB/s, the card's rate.
+// The route depends on no weight layout: packed and row-major weights give the
+// same bits.
 constexpr int32_t kMidMinTokens = 65;
-static bool use_mid(const eat_params_t& p, int32_t T) {
-    return p.expert_dtype == EAT_BF16 && T >= kMidMinTokens && !use_wide(p, T) && mid_fits(p.d_ffn, p.d_model) &&
-           mid_fits(p.d_model, p.d_ffn);
+
+// EAT concentrates its picks on about K experts (under the share reading of
+// C_s they spread like Top-K's).
+static bool concentrates(const eat_params_t& p) { return p.mode == EAT_MODE_EAT && p.cs_mode == 0; }
+
+// The exception: an EAT call of up to 96 tokens whose K experts make items for
+// less than half of the CUs (a tile's workgroup walks the whole reduction, the
+// streaming kernel's items share it), where the streaming kernel reads the down
+// projection's rows in deep chunks (d_ffn a multiple of 256).  8 of 128 experts
+// 768 wide, 96 items: 62-66 us at 65-96 tokens against 70-71 (row-major 65-70,
+// 70-71), 128 tokens row-major 75 against 73; 4 of 60 experts 1408 wide, 88 items,
+// an odd number of chunks: 101-107 against 95-98.  And where its gate/up partials
+// fit in the down projection's slices (plan_workspace), so that it takes no more
+// workspace than the tiles.
+static int stream_up_splits(const eat_params_t& p, int32_t T);
+static bool few_items(const eat_params_t& p, int32_t T) {
+    return concentrates(p) && T <= 96 && int64_t{p.top_k} * (p.d_ffn / 64) < kRoundItems / 2 && p.d_ffn % 256 == 0 &&
+           int64_t{2} * stream_up_splits(p, T) * p.d_ffn <= int64_t{down_splits(p, T)} * p.d_model;
 }
-// 256-row token tiles where an expert is expected to hold about 100 rows or
-// more (many then exceed 128, and a second 128-row tile reads the weights
+static bool use_mid(const eat_params_t& p, int32_t T) {
+    return p.expert_dtype == EAT_BF16 && T >= kMidMinTokens && !use_wide(p, T) && !few_items(p, T) &&
+           mid_fits(p.d_ffn, p.d_model) && mid_fits(p.d_model, p.d_ffn);
+}
+// 256-row token tiles over `groups` evenly loaded experts: from about 100 rows
+// per expert (many then exceed 128, and a second 128-row tile reads the weights
 // again: 8 experts of ~125 rows 240 against 335 us down, 495 against 553
-// up/gate) and the up/gate projection's 64-feature items still reach every CU
+// up/gate), where the up/gate projection's 64-feature items still reach every CU
 // (8 experts of 256 rows, 128 items: 38 against 31 us).
-static bool mid_tall(int64_t groups, int64_t rows, int M) {
+static bool even_tall(int64_t groups, int64_t rows, int M) {
     const int64_t per = (rows + groups - 1) / std::max<int64_t>(1, groups);
-    return per >= 96 && groups * ((per + 255) / 256) * (M / 64) >= 256;
+    return per >= 96 && groups * ((per + 255) / 256) * (M / 64) >= kRoundItems;
+}
+// An EAT call's experts hold up to T rows each: the tile with the shorter
+// up/gate launch, in rounds of kRoundItems items times a chunk's time, over the
+// experts such a call touches (K; of more than 256 tokens up to a quarter more).
+// One tile more than a round costs a whole one: 9 of 64 experts, 320 tokens, 288
+// Tall items, 137 us against 110 on 128-row tiles (432, also two rounds); 8 of 128
+// experts, 512 tokens, 127 us on 128-row tiles (384 items) against 112 (192).
+static bool eat_tall(const eat_params_t& p, int32_t T) {
+    const int K = std::min(p.top_k, p.E);
+    const int more = T > kFusedTokens;
+    const int experts[3] = {K, std::min(p.E, K + more * (K / 8)), std::min(p.E, K + more * ((K + 2) / 4))};
+    int64_t mid = 0, tall = 0;
+    for (const int e : experts) {
+        const int64_t row = static_cast<int64_t>(e) * (p.d_ffn / 64);
+        mid += (row * ((T + 127) / 128) + kRoundItems - 1) / kRoundItems * kMidChunkNs;
+        tall += (row * ((T + 255) / 256) + kRoundItems - 1) / kRoundItems * kTallChunkNs;
+    }
+    return tall < mid;
+}
+// Top-P tokens select as many experts as reach top_p, not top_k.  The host
+// knows the count no better than E top_p / 5 (at top_p = 0.6: 1 of 8, where 1.3
+// were measured, 7.2 of 60 (6.5), 7.7 of 64 (6.7), 15 of 128 (11)).  With top_k the
+// Mixtral-shaped layer went Tall from 384 tokens: 590 us against 557.
+static bool mid_tall(const eat_params_t& p, int32_t T) {
+    if (concentrates(p)) return eat_tall(p, T);
+    double each = p.top_k;
+    if (p.mode == EAT_MODE_TOPP) each = std::max(1.0, 0.2 * p.E * p.top_p);
+    if (p.mode == EAT_MODE_TOPP && p.top_p_cap > 0) each = std::min<double>(each, p.top_p_cap);
+    const int64_t rows = static_cast<int64_t>(T * each);
+    return even_tall(std::min<int64_t>(p.E, rows), rows, p.d_ffn);
 }
 static bool shared_wide(const eat_params_t& p, int32_t T) {
     return T >= 384 && p.d_shared > 0 && wide_fits(true, p.d_shared, p.d_model) &&
@@ -1009,10 +1060,14 @@ static int up_kin(const eat_params_t& p, int32_t T) {
     return up_groups(p.d_ffn, p.d_model, expected_tiles(p, T), up_threshold(T));
 }
 
-int up_splits(const eat_params_t& p, int32_t T) {
-    if (p.expert_dtype != EAT_BF16 || use_wide(p, T) || use_mid(p, T)) return 1;
+static int stream_up_splits(const eat_params_t& p, int32_t T) {
     const int kin = up_kin(p, T);
     return split_rule(p.d_ffn * kin, p.d_model / kin, expected_tiles(p, T), EAT_UP_SPLIT_MAX, up_threshold(T), true);
+}
+
+int up_splits(const eat_params_t& p, int32_t T) {
+    if (p.expert_dtype != EAT_BF16 || use_wide(p, T) || use_mid(p, T)) return 1;
+    return stream_up_splits(p, T);
 }
 
 // Dense projection (one group of T identity rows): the wide tiles from 384
@@ -1105,9 +1160,7 @@ hipError_t launch_experts_bf16(const eat_params_t& p, int32_t T, int64_t rows_ca
                            rows_bf16(p, T) ? nrm2 : nullptr, s);
     }
     if (use_mid(p, T)) {
-        const int64_t assign = static_cast<int64_t>(T) * p.top_k;
-        const bool tall = mid_tall(std::min<int64_t>(p.mode == EAT_MODE_EAT && p.cs_mode == 0 ? p.top_k : p.E, assign),
-                                   assign, p.d_ffn);
+        const bool tall = mid_tall(p, T);
         hipError_t err = launch_mid(true, tall, w1, w3, x, tok_idx, offsets, p.E, 0, p.d_ffn, p.d_model, h, rows_cap, packed,
                                     1, 0, nullptr, seg, s);
         if (err != hipSuccess) return err;
@@ -1175,7 +1228,7 @@ int shared_up_splits(const eat_params_t& p, int32_t T) {
 int shared_splits(const eat_params_t& p, int32_t T) {
     if (p.expert_dtype != EAT_BF16 || p.d_shared == 0 || shared_wide(p, T)) return 1;
     if (shared_mid(p, T)) {
-        const bool tall = mid_tall(1, T, p.d_shared);
+        const bool tall = even_tall(1, T, p.d_shared);
         const int tm = tall ? 256 : 128;
         return tile_split(static_cast<int64_t>((T + tm - 1) / tm) * ((p.d_model + 127) / 128), p.d_shared,
                           dense_splits(p.d_model, p.d_shared, T), T, p.d_model, tall ? kTallChunkNs : kMidChunkNs);
@@ -1205,7 +1258,7 @@ hipError_t launch_shared_bf16(const eat_params_t& p, int32_t T, const uint16_t* 
         return hipGetLastError();
     };
     if (shared_mid(p, T)) {
-        const bool tall = mid_tall(1, T, p.d_shared);
+        const bool tall = even_tall(1, T, p.d_shared);
         hipError_t err = launch_mid(true, tall, ws1, ws3, x, nullptr, nullptr, 1, T, p.d_shared, p.d_model, hs, T,
                                     packed, 1, 0, nullptr, {}, s);
         if (err != hipSuccess) return err;

@@ -44,3 +44,56 @@ def test_every_call_builds_its_permutation(tmp_path):
         assert permutes + fused == layers, (c, names)
         wide += c["T"] == 256 and "Tile<256, 256" in ups[0]
     assert wide > 0                               # the calls where the two sizes meet are among them
+
+
+def _up(g):
+    return next(n for n, _ in g["kernels"] if "stream_kernel<true" in n or "wide_kernel<true" in n)
+
+
+def _tile(name):
+    for tile, text in (("wide", "Tile<256, 256"), ("tall", "Tile<256, 128"), ("mid", "Tile<128, 128")):
+        if text in name:
+            return tile
+    assert "stream_kernel" in name
+    return "stream"
+
+
+# (E, top_k, d_model, d_ffn), mode (0 EAT, 1 Top-K, 2 Top-P), tokens -> the kernel
+# that measured faster there
+MIXTRAL, FINE, QWEN = (8, 2, 4096, 14336), (64, 8, 2048, 1024), (128, 8, 2048, 768)
+ROUTES = [(MIXTRAL, 0, 64, "stream"), (MIXTRAL, 0, 96, "mid"), (MIXTRAL, 0, 128, "mid"), (MIXTRAL, 0, 160, "tall"),
+          (MIXTRAL, 0, 320, "mid"), (MIXTRAL, 0, 384, "mid"), (MIXTRAL, 0, 512, "tall"), (MIXTRAL, 0, 768, "tall"),
+          (MIXTRAL, 2, 384, "mid"), (MIXTRAL, 2, 800, "tall"), (MIXTRAL, 1, 500, "tall"), (MIXTRAL, 1, 1024, "wide"),
+          (FINE, 0, 65, "mid"), (FINE, 0, 256, "mid"), (FINE, 0, 320, "mid"), (FINE, 0, 384, "mid"),
+          (FINE, 0, 1024, "tall"), (FINE, 2, 512, "mid"), (FINE, 2, 1024, "tall"), (FINE, 1, 768, "tall"),
+          (QWEN, 0, 65, "stream"), (QWEN, 0, 96, "stream"), (QWEN, 0, 97, "mid"), (QWEN, 0, 384, "tall"),
+          (QWEN, 0, 512, "tall"), (QWEN, 0, 640, "mid"), (QWEN, 1, 65, "mid"), (QWEN, 2, 1500, "tall")]
+
+
+def test_medium_calls_take_the_faster_tile(tmp_path):
+    """The up/gate kernel of calls of more than 64 tokens, the same for both
+    weight layouts (which give the same bits)."""
+    calls = [dict(kind="forward", T=T, mode=mode, E=s[0], top_k=s[1], d_model=s[2], d_ffn=s[3], top_p=0.6,
+                  weight_layout=lay) for s, mode, T, _ in ROUTES for lay in (L.EAT_LAYOUT_ROWS, L.EAT_LAYOUT_PACKED)]
+    got = list_launches(tmp_path, calls)
+    for i, (s, mode, T, want) in enumerate(ROUTES):
+        assert [_tile(_up(g)) for g in got[2 * i:2 * i + 2]] == [want] * 2, (s, mode, T)
+
+
+def test_streaming_route_needs_no_more_workspace(tmp_path):
+    """Calls of 65 to 96 tokens that go to the streaming kernel hold its gate/up
+    partials where the down projection's slices go later: no call of that size
+    that fits a given scratch on the tiles (one token more) stops fitting."""
+    shapes = [(16, 4, 1024, 1024), (128, 8, 2048, 768), (64, 1, 512, 4096), (8, 1, 256, 7936), (32, 8, 192, 256),
+              (128, 2, 4096, 256)]
+    calls = [dict(kind="forward", T=T, mode=0, E=E, top_k=K, d_model=d, d_ffn=F) for E, K, d, F in shapes
+             for T in (65, 80, 96, 97)]
+    got = list_launches(tmp_path, calls)
+    streams = 0
+    for i in range(0, len(calls), 4):
+        per = [g["bytes"] / c["T"] for g, c in zip(got[i:i + 4], calls[i:i + 4])]
+        streams += _tile(_up(got[i])) == "stream"
+        for g, c, b in zip(got[i:i + 4], calls[i:i + 4], per):
+            # h and the slices of the down projection, the tiles' two large regions, and the rest
+            assert b <= 1.03 * per[3], (c, per)
+    assert streams >= 2
