@@ -2,12 +2,12 @@
 // (Sec. 3.3), gfx950.
 //
 // The LM-head projection z = h W_V^T runs on the MFMA tiles (wide.hip) into
-// fp32 rows, or on the streaming kernel (expert.hip) where the reduction is too
-// short for them (up to two slices of it, added in order here).
+// fp32 rows, or on the streaming kernel (expert.hip) where it is the faster or
+// the reduction too short for them (up to two slices of it, added in order here).
 // ppl_kernel, one workgroup per sequence, folds the row into an online
 // logsumexp pair (running max, sum of exp(z - max)): a thread's values a block
-// at a time, then the wave by butterfly, then the waves in order; its first
-// thread forms the NLL from it and z[target] and the sequence's running state in
+// at a time, then the lanes of a wave and then the waves over their maximum; its
+// first thread forms the NLL from it and z[target] and the sequence's running state in
 // fp64: sum of NLL, token count, perplexity exp(sum / count) and the trend (+1
 // rose since the previous token, -1 did not, 0 first token).  Every merge has a
 // fixed order, so results are bit-reproducible.
@@ -39,14 +39,24 @@ __device__ __forceinline__ Lse lse_merge(Lse a, Lse b) {
     return {a.m, a.s + b.s * term(b.m, a.m)};
 }
 
+// The pairs of a wave's lanes, over their maximum.
+__device__ __forceinline__ Lse lse_wave(Lse a) {
+    const float m = wave_max(a.m);
+    return {m, wave_sum(a.s * term(a.m, m))};
+}
+
 // One workgroup per sequence: 128 KB of logits are a latency and a few us for
 // a CU, less than the launch that a split over more workgroups needs to merge
-// its parts (16 chunks a row, 256 threads each, and a finishing launch: 14.4 us
-// at 64 x 32000 against 6.5).
+// its parts.  1 sequence of 32000, 8.2 us, 16 chunks of 256 threads and a finishing
+// launch 12.3 (64 sequences 9.6 and 13.5; 1 of 128256 23.7 and 26.6).  What a
+// sequence waits for is a chain, so every load that needs no other is issued
+// first: with the target, its head row and the state loaded where they are used,
+// the waves' pairs merged one by one and a log more, it took 2 us longer.
 // The target's logit, on whose rounding the NLL would depend most, is taken
 // again from the hidden row and the head's row in fp64 (16 KB, under the logits'
 // latency), on both sides of the NLL: the row's logsumexp leaves the target out,
-// and NLL = log(1 + exp(rest - z[target])).  It is never negative, and its
+// and NLL = log(1 + exp(rest - z[target])) = log1p(s exp(m - z[target])), or
+// m - z[target] + log(s + exp(z[target] - m)) below m.  It is never negative, and its
 // error is the rest's times the probability of the rest, however confident the
 // prediction.
 __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__ z, int splits, int64_t stride, int V,
@@ -57,10 +67,23 @@ __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__
                                                        float* nll_out) {
     __shared__ Lse red[kWaves];
     __shared__ double zred[kWaves];
-    const int s = blockIdx.x;
+    const int s = blockIdx.x, lane = lane_id(), wave = threadIdx.x / kWave;
     const float* row = z + static_cast<size_t>(s) * V;
     const int y = target[s];
     const bool known = y >= 0 && y < V;
+    const double sum0 = nll_sum[s], prev = ppl_prev[s];
+    const int32_t n0 = count[s];
+    // a block of a thread's logits (V is a multiple of 64; columns past V read the block's first)
+    auto load = [&](int j0, float4 (&v)[kVec]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kVec; ++i) {
+            const int j = j0 + 4 * kThreads * i;
+            v[i] = *reinterpret_cast<const float4*>(row + (j < V ? j : j0));
+        }
+    };
+    const int jbeg = 4 * threadIdx.x;
+    float4 v[kVec] = {};
+    if (jbeg < V) load(jbeg, v);
     double zt = 0.0;
     for (int k = 4 * threadIdx.x; k < d; k += 4 * kThreads) {     // (d is a multiple of 64)
         const uint2 p = *reinterpret_cast<const uint2*>(h + static_cast<size_t>(s) * d + k);
@@ -75,16 +98,8 @@ __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__
         }
     }
     zt = wave_sum(zt);
-    if (lane_id() == 0) zred[threadIdx.x / kWave] = zt;
     Lse a{-INFINITY, 0.f};
-    // (V is a multiple of 64)
-    for (int j0 = 4 * threadIdx.x; j0 < V; j0 += 4 * kThreads * kVec) {
-        float4 v[kVec];
-#pragma unroll
-        for (int i = 0; i < kVec; ++i) {
-            const int j = j0 + 4 * kThreads * i;
-            v[i] = *reinterpret_cast<const float4*>(row + (j < V ? j : j0));
-        }
+    for (int j0 = jbeg; j0 < V; j0 += 4 * kThreads * kVec) {
         for (int sp = 1; sp < splits; ++sp)
 #pragma unroll
             for (int i = 0; i < kVec; ++i) {
@@ -109,32 +124,30 @@ __global__ __launch_bounds__(kThreads) void ppl_kernel(const float* __restrict__
             if (j0 + 4 * kThreads * i < V)
                 b.s += (term(v[i].x, b.m) + term(v[i].y, b.m)) + (term(v[i].z, b.m) + term(v[i].w, b.m));
         if (b.m == -INFINITY) b.s -= b.s;     // no logit above -inf: 0, or NaN
+        const int jn = j0 + 4 * kThreads * kVec;
+        if (jn < V) load(jn, v);
         a = lse_merge(a, b);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const Lse b{__shfl_xor(a.m, off, kWave), __shfl_xor(a.s, off, kWave)};
-        // merge in a fixed (lower lane first) order so partners agree bit for bit
-        a = (lane_id() & off) ? lse_merge(b, a) : lse_merge(a, b);
+    a = lse_wave(a);
+    if (lane == 0) {
+        red[wave] = a;
+        zred[wave] = zt;
     }
-    if (lane_id() == 0) red[threadIdx.x / kWave] = a;
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    Lse t = red[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) t = lse_merge(t, red[w]);
-    zt = zred[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) zt += zred[w];
-    const double rest = static_cast<double>(t.m) + log(static_cast<double>(t.s));
+    if (wave != 0) return;
+    a = lane < kWaves ? red[lane] : Lse{-INFINITY, 0.f};
+    zt = wave_sum(lane < kWaves ? zred[lane] : 0.0);
+    a = lse_wave(a);
+    if (lane != 0) return;
+    const double m = static_cast<double>(a.m), rest = static_cast<double>(a.s);
     // (zt - zt is NaN for an infinite target, as its row's logsumexp less itself)
     const double nll = !known ? NAN
-                       : zt >= rest ? log1p(exp(rest - zt)) + (zt - zt)
-                                    : rest - zt + log1p(exp(zt - rest));
-    const double sum = nll_sum[s] + nll;
-    const int32_t n = count[s] + 1;
+                       : zt >= m ? log1p(rest * exp(m - zt)) + (zt - zt)
+                                 : m - zt + log(rest + exp(zt - m));
+    const double sum = sum0 + nll;
+    const int32_t n = n0 + 1;
     const double ppl = exp(sum / n);
-    trend[s] = n > 1 ? (ppl > ppl_prev[s] ? 1 : -1) : 0;
+    trend[s] = n > 1 ? (ppl > prev ? 1 : -1) : 0;
     nll_sum[s] = sum;
     count[s] = n;
     ppl_prev[s] = ppl;
