@@ -1105,7 +1105,22 @@ hipError_t launch_dense_bf16(const uint16_t* src, int32_t T, const uint16_t* w, 
 // (3.9 TB/s) in the streaming kernel's two slices and the whole signal 72.6; on
 // the tiles 59.1 (1 sequence 63.6 -> 54.9, 200 sequences, on 256-row tiles,
 // 147 -> 101, 383 205 -> 178).
-static bool head_mid(int M, int K, int32_t T) { return !dense_wide(M, K, T) && mid_fits(M, K); }
+// A head of a little over kRoundItems 128-row weight tiles takes a second round
+// of mostly idle CUs, though: up to 64 sequences go to the streaming kernel where
+// it reads the head (4.4 TB/s, less with more sequences) in less than 1.1 times
+// the tiles' rounds.  Whole signal, heads out of cache, d 4096: V = 32832, 1
+// sequence 91 us on the tiles, 71 streamed, 32 sequences 95 and 84, 64 97 and 94;
+// V = 40000, 1 sequence 89 and 76, 32 93 and 91; V = 49152, 1 sequence 87 and 97.
+// In one round the tiles lose nothing over 3 us (16000 x 4096, 1 sequence, 42
+// against 39), from 96 sequences nothing.
+static bool head_mid(int M, int K, int32_t T) {
+    if (dense_wide(M, K, T) || !mid_fits(M, K)) return false;
+    const int64_t rounds = ((M + 127) / 128 + kRoundItems - 1) / kRoundItems;
+    if (rounds == 1 || T > 64) return true;
+    const int64_t tiles_ns = rounds * (K / 64) * kMidChunkNs;
+    const int64_t stream_ns = int64_t{2} * M * K / 4400 * (160 + T) / 160;
+    return 10 * stream_ns >= 11 * tiles_ns;
+}
 
 // Most slices of the head where the streaming kernel runs it (each costs one
 // more S x V fp32 read in the logsumexp).

@@ -97,3 +97,18 @@ def test_streaming_route_needs_no_more_workspace(tmp_path):
             # h and the slices of the down projection, the tiles' two large regions, and the rest
             assert b <= 1.03 * per[3], (c, per)
     assert streams >= 2
+
+
+def test_head_just_over_a_round_of_tiles_streams(tmp_path):
+    """The LM head of few sequences a little over 256 weight tiles of 128 rows
+    (32768) would pay a second, nearly empty round on the tiles."""
+    routes = [(1, 4096, 32768, "mid"), (1, 4096, 32832, "stream"), (64, 4096, 32000, "mid"), (32, 4096, 32832, "stream"),
+              (1, 2048, 40000, "stream"), (64, 4096, 40000, "mid"), (1, 4096, 50304, "mid"), (96, 4096, 32832, "mid"),
+              (1, 4096, 128256, "mid"), (129, 4096, 32832, "tall"), (384, 4096, 32832, "tall"), (384, 4096, 32768, "wide"),
+              (3, 128, 64, "stream")]
+    got = list_launches(tmp_path, [dict(kind="ppl", T=S, d=d, V=V) for S, d, V, _ in routes])
+    for (S, d, V, want), g in zip(routes, got):
+        name, (_, _, _, threads) = g["kernels"][0]
+        assert _tile(name) == want, (S, d, V, name)
+        # logits of two reduction slices at most
+        assert 4 * S * V <= g["bytes"] <= 8 * S * V + 256
