@@ -20,9 +20,9 @@
 // Weights may be in the packed layout (pack.hip), read one contiguous
 // kilobyte per load instruction with the streaming cache policy.
 // Calls of more than 64 tokens go to the MFMA tiles of wide.hip instead,
-// unless d_model or d_ffn is too short for their ring (below 192); the
-// 128-token tiles here serve those layers and the mixing projection of stacked
-// layers.  (Figures below for 128-token tiles on the named layers' calls of more
+// unless d_model or d_ffn is too short for their ring (below 192) or their
+// items leave most CUs idle (few_items); the 128-token tiles here serve those
+// calls and the mixing projection of stacked layers.  (Figures below for 128-token tiles on the named layers' calls of more
 // than 64 tokens were measured when those calls still ran here.)
 //
 // fp32 path: fp32 MFMA tiles, for layers whose weights are fp32 (small
@@ -946,7 +946,7 @@ static bool use_wide(const eat_params_t& p, int32_t T) {
 // for the streaming kernel's 128-token tiles.  Measured against those (whole
 // layer): Mixtral-shaped, 500 tokens over 8 experts, 870-890 -> 750-775 us;
 // 128 experts, 1000 tokens, 375 -> 311; 60 experts, 128 tokens, 315 -> 250;
-// 8 of 64 experts, 256 tokens, 89 -> 74.  Up to 64 tokens the streaming
+// 8 of 64 experts, 256 tokens, 94 -> 81.  Up to 64 tokens the streaming
 // kernel reads packed weights at 5.8-6.1 TB/s, the card's rate.
 // The route depends on no weight layout: packed and row-major weights give the
 // same bits.

@@ -14,9 +14,10 @@
 // Three tiles (measured on the expert loads of real calls; up/gate us):
 //   Wide 256 x 256, 2 stages: prefill-sized calls (hundreds of rows per
 //     expert).  64 experts of ~512 rows: 345 us; the 256 x 128 tile 353, the
-//     128 x 128 one 440.  Bound by the operand bytes a CU can pull through its
-//     vector L1 (about 33 GB/s per CU of mixed L2 hits and misses, however
-//     deep the ring), which only a larger tile area lowers.
+//     128 x 128 one 440.  Bound by the operand bytes a CU pulls through its vector
+//     L1: the tile moves about 33 GB/s per CU however deep the ring (a probe of
+//     such loads alone, L2 hits and misses mixed, all CUs, 45), and only a
+//     larger tile area needs fewer bytes.
 //   Tall 256 x 128, 3 stages: about 100 rows per expert and up.  8 experts of
 //     ~125 rows, 14336 x 4096: 478-497 us against 520-560 with the 128 x 128
 //     tile, which reads the weights of an expert with more than 128 rows twice.
@@ -26,7 +27,7 @@
 // Against the streaming kernel (expert.hip) with 128-token tiles, whose waves
 // keep 24 KB of weights in flight per CU: qwen3-shaped 1000-token Top-K call,
 // whole layer, 379 -> 316 us; shared-expert layer's 128-token Top-P decode
-// 316 -> 250; fine-grained 256-token EAT decode 93 -> 81.
+// 316 -> 250; fine-grained 256-token EAT decode 94 -> 81.
 //
 // The grid is persistent: the work list (per expert, its weight tiles in
 // turn and each one's token tiles adjacent) is cut into contiguous parts,

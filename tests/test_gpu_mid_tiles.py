@@ -71,3 +71,28 @@ def test_head_tiles(S, d, V):
     nll = torch.logsumexp(z, 1) - z.gather(1, target.long()[:, None])[:, 0]
     bound = 2 * d * 2.0 ** -24 * (h.double().abs() @ head.double().abs().T).max() + 16 * 2.0 ** -24 * (1 + nll.abs().max())
     assert (sig.nll.cpu().double() - nll).abs().max() <= bound
+
+
+@pytest.mark.parametrize("S,d,V", [(1, 192, 64), (16, 256, 960), (128, 192, 320), (129, 512, 1088), (383, 256, 448),
+                                   (384, 256, 512), (3, 128, 192), (40, 256, 33024), (64, 192, 32832)])
+def test_every_head_column_counts_once(S, d, V):
+    """Hidden rows along one head row each, c: its logit, 15, carries the
+    sequence's logsumexp, so a lost column moves the NLL by several units and a
+    repeated one by log 2 (all columns of small heads; of large ones the first and
+    last tiles).  The bound is that of test_head_tiles, per sequence."""
+    g = torch.Generator().manual_seed(S + d + V)
+    head = (torch.randn(V, d, generator=g) * d ** -0.5).to(torch.bfloat16)
+    cols = torch.arange(V) if V <= 1100 else torch.cat([torch.arange(130), torch.arange(V - 330, V)])
+    sig = PplSignal(S, head.cuda())
+    for i in range(0, len(cols), S):
+        c = cols[torch.arange(i, i + S) % len(cols)]
+        h = (15.0 * head[c].float() / head[c].float().square().sum(1, keepdim=True)).to(torch.bfloat16)
+        target = (c + V // 2) % V
+        sig.reset()
+        sig.step(h.cuda(), target.to(torch.int32).cuda())
+        torch.cuda.synchronize()
+        z = h.double() @ head.double().T
+        nll = torch.logsumexp(z, 1) - z.gather(1, target[:, None])[:, 0]
+        bound = 2 * d * 2.0 ** -24 * (h.double().abs() @ head.double().abs().T).max(1).values + 16 * 2.0 ** -24 * (1 + nll)
+        assert bound.max() < 0.05
+        assert ((sig.nll.cpu().double() - nll).abs() <= bound).all(), (i, S, d, V)
