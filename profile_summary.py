@@ -66,12 +66,13 @@ def counter_rows(d):
     return list(csv.DictReader(open(os.path.join(d, "run_counter_collection.csv"))))
 
 
-def copy_factor(rows, mib: int, expect_bytes: float) -> float:
-    """Bytes a known-size copy really moves / what the counter reports for it."""
-    vals = [float(r["Counter_Value"]) * 1024 for r in rows
-            if COPY in r["Kernel_Name"] and int(r["Grid_Size"]) >= 65536]
+def copy_factor(rows, total_bytes: float) -> float:
+    """Bytes the calibration copies move / what the counter reports for them
+    (the dispatches near the largest count; a long run copies its inputs too)."""
+    vals = [float(r["Counter_Value"]) * 1024 for r in rows if COPY in r["Kernel_Name"]]
     assert vals, "no calibration copy dispatch found"
-    return expect_bytes / statistics.mean(vals)
+    vals = [v for v in vals if v > 0.5 * max(vals)]
+    return total_bytes / sum(vals)
 
 
 BF16_PEAK_TFLOPS = 2500.0
@@ -183,7 +184,7 @@ def layer_decode_summary(args) -> int:
         for tot, name, n_per, avg in sorted(rows, reverse=True):
             f.write(f"| `{name}` | {n_per:.2f} | {avg:.2f} | {tot:.2f} |\n")
         f.write(f"| **sum** | | | **{sum(x[0] for x in rows):.1f}** |\n")
-        if up:
+        if up and not dl.get('d_shared'):     # (the always-on expert runs the same kernel)
             us = sum(x[0] for x in up)
             fl = 4.0 * d * F * sk
             wb = r["mean_experts_touched_per_step"] * 4.0 * d * F
@@ -268,10 +269,9 @@ def main(argv=None) -> int:
 
     # counters: the copy kernel is a (split) 1 GiB read + 1 GiB write in 512 MiB dispatches
     fetch, write = counter_rows(args.fetch), counter_rows(args.write)
-    copy_disp = [r for r in fetch if COPY in r["Kernel_Name"] and int(r["Grid_Size"]) >= 65536]
-    per_copy = args.copy_mib * (1 << 20) * 4 / len(copy_disp)       # bytes each dispatch moves
-    f_fac = copy_factor(fetch, args.copy_mib, per_copy)
-    w_fac = copy_factor(write, args.copy_mib, per_copy)
+    copied = args.copy_mib * (1 << 20) * 4
+    f_fac = copy_factor(fetch, copied)
+    w_fac = copy_factor(write, copied)
     fd = [float(r["Counter_Value"]) * 1024 * f_fac for r in fetch if DOMINANT in r["Kernel_Name"]][-args.steps:]
     wd = [float(r["Counter_Value"]) * 1024 * w_fac for r in write if DOMINANT in r["Kernel_Name"]][-args.steps:]
     fetch_b, write_b = statistics.mean(fd), statistics.mean(wd)
