@@ -165,8 +165,8 @@ eat_status_t eat_destroy(eat_handle_t h);
  * mode's largest possible number of (token, expert) assignments (T*K for
  * Top-K, T*E for EAT and uncapped Top-P, since Eq. 6 keeps exact ties and
  * the nucleus is unbounded).  It is not monotonic in T: fewer tokens can
- * mean more slices (e.g. the Mixtral-shaped EAT layer needs more at T = 128
- * than at T = 129), so size a reused workspace by the largest value over the
+ * mean more slices (e.g. an EAT layer of 64 experts of width 1024, d_model 2048,
+ * top_k 8 needs more at T = 128 than at T = 129), so size a reused workspace by the largest value over the
  * T a caller will pass. */
 eat_status_t eat_workspace_size(eat_handle_t h, int32_t T, size_t* bytes);
 
@@ -367,7 +367,7 @@ eat_status_t eat_pack_weights(const void* src, int32_t groups, int32_t M, int32_
  * current (make that first call outside graph capture).
  *   Limit: a call whose eat_workspace_size(h, T) exceeds
  *   EAT_NOALLOC_SCRATCH_BYTES returns EAT_ERR_SCRATCH_LIMIT and enqueues
- *   nothing (e.g. the Mixtral-shaped EAT layer fits up to T = 64 tokens).
+ *   nothing (e.g. the Mixtral-shaped EAT layer fits up to T = 209 tokens).
  *   Sharing: every call on one GPU uses that GPU's one array, and no part
  *   of it needs clearing (each call writes every byte it reads first), so
  *   consecutive calls are independent; calls whose executions overlap on

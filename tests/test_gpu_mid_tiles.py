@@ -22,6 +22,9 @@ CASES = {
     "tall": dict(shape="mixtral", d=256, F=2048, E=8, Fs=0),
     # few rows over many experts, an always-on expert of its own tiles
     "many": dict(shape="shared", d=320, F=192, E=60, Fs=448),
+    # EAT's 8 experts make 64 items: the streaming kernel's 128-token tiles up to 96
+    # tokens, with gate/up partials in the down projection's slices
+    "few": dict(shape="finegrained", d=1024, F=512, E=64, Fs=0),
 }
 
 
@@ -29,6 +32,7 @@ CASES = {
     ("short", 65, "topk"), ("short", 128, "eat"), ("short", 129, "eat"), ("short", 513, "topk"),
     ("tall", 384, "topk"), ("tall", 520, "topp"), ("tall", 900, "eat"), ("tall", 70, "eat"),
     ("many", 65, "topp"), ("many", 257, "eat"), ("many", 300, "topk"),
+    ("few", 65, "eat"), ("few", 96, "eat"), ("few", 97, "eat"), ("few", 96, "topk"),
 ])
 def test_mid_tiles(case, T, mode):
     c = CASES[case]
