@@ -188,8 +188,8 @@ __device__ __forceinline__ uint64_t bit_transpose(uint64_t m) {
 // thread of the workgroup (NW waves) calls it; cols and soff are LDS.  A lane
 // per token, a bit transpose per 64 tokens and mask word, so it costs about
 // what reading the arrays of a permutation launch would, whose ~4 us it saves
-// (16-layer EAT decode of 64 tokens 1068 -> 1032 us a step, Mixtral-shaped 64
-// tokens 202 -> 198, the 32-token fp32 layer 31 -> 28; with a ballot per expert
+// (16-layer EAT decode of 64 tokens 1068 -> 1032 us a step, the 32-token fp32
+// layer 31 -> 28; layers of big experts within the noise; with a ballot per expert
 // in place of the transpose the 64-expert layers gained nothing).
 template <int NW, int NC>
 __device__ __forceinline__ void build_segments(const uint64_t* __restrict__ mask, int T, int E, int W, uint64_t* cols,
